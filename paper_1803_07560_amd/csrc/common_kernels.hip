@@ -219,12 +219,7 @@ __global__ void __launch_bounds__(256) nsphere_kernel(NsphereArgs na)
                 acc[2 + kMaxNsphereDim + kk] += up ? f2 : 0.0;
             }
         }
-#pragma unroll
-        for (int i = 0; i < kF; ++i) {
-            const double v = dev::wave_sum(acc[i]);
-            if (lane == 0)
-                red[wave][i] = v;
-        }
+        dev::wave_sums<kF>([&](int i) { return acc[i]; }, red[wave], lane);
         __syncthreads();
         for (int i = tid; i < kF; i += kBlock) {
             double total = 0.0;

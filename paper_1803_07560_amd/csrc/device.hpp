@@ -373,6 +373,76 @@ __device__ __forceinline__ double wave_sum(double v)
     return v;
 }
 
+// x of the lane `CTRL` selects within the row of 16 (a data-parallel move: one
+// vector instruction per dword, no trip through LDS).
+template <int CTRL>
+__device__ __forceinline__ double row_move(double x)
+{
+    const uint64_t b = __builtin_bit_cast(uint64_t, x);
+    const int lo = static_cast<int>(b), hi = static_cast<int>(b >> 32);
+    const uint32_t l = __builtin_amdgcn_update_dpp(lo, lo, CTRL, 0xf, 0xf, false);
+    const uint32_t h = __builtin_amdgcn_update_dpp(hi, hi, CTRL, 0xf, 0xf, false);
+    return __builtin_bit_cast(double, static_cast<uint64_t>(h) << 32 | l);
+}
+// Rotation within the row of 16 by R lanes.
+template <int R>
+__device__ __forceinline__ double row_rotate(double x)
+{
+    return row_move<0x120 + R>(x);
+}
+
+// One halving step of a many-field wavefront sum: the lanes of the first half
+// (of the wavefront for ROWS = 2, of each pair of rows for ROWS = 1) go on with
+// field a, those of the second half with field b, each holding its own value
+// plus its partner lane's.  The swap exchanges a's second half with b's first.
+template <int ROWS>
+__device__ __forceinline__ double halve(double a, double b)
+{
+    const uint64_t x = __builtin_bit_cast(uint64_t, a), y = __builtin_bit_cast(uint64_t, b);
+    const uint32_t xl = static_cast<uint32_t>(x), xh = static_cast<uint32_t>(x >> 32);
+    const uint32_t yl = static_cast<uint32_t>(y), yh = static_cast<uint32_t>(y >> 32);
+    const auto lo = ROWS == 2 ? __builtin_amdgcn_permlane32_swap(xl, yl, false, false)
+                              : __builtin_amdgcn_permlane16_swap(xl, yl, false, false);
+    const auto hi = ROWS == 2 ? __builtin_amdgcn_permlane32_swap(xh, yh, false, false)
+                              : __builtin_amdgcn_permlane16_swap(xh, yh, false, false);
+    return __builtin_bit_cast(double, static_cast<uint64_t>(hi[0]) << 32 | lo[0]) +
+           __builtin_bit_cast(double, static_cast<uint64_t>(hi[1]) << 32 | lo[1]);
+}
+
+// Sums of N fields over the wavefront, field i = value(i), into out[i] (LDS).
+// A butterfly per field moves every field through all six exchange steps; here
+// the first two steps halve the fields instead (each half, then each row, of
+// the wavefront goes on with its own), so four fields share a register for the
+// last four, which rotate within a row of 16.  The additions are those of
+// wave_sum -- lane distances 32, 16, 8, 4, 2, 1, the same two operands in some
+// order -- so the sums are the same bits.  What bounds it is instruction issue:
+// about 5 vector instructions per field against 18 with 12 of them LDS
+// permutes, which is what an item of few samples per thread spent its time on.
+// Measured, butterfly per field -> this: a burst of 16 served requests (FP32
+// form, 2^16 .. 2^22 evaluations each) 1.50 -> 1.42 ms, 2^27 evaluations of 8x2
+// as FP64 pairs (128 items a CU) 1.052 -> 1.037 ms, a 4x2 call of 2^16
+// evaluations 238 -> 225 us; items of 1024 samples per thread the same.
+template <int N, class Value>
+__device__ __forceinline__ void wave_sums(Value &&value, double *out, uint32_t lane)
+{
+    constexpr int Q = (N + 3) / 4, H = 2 * Q;
+    const uint32_t row = lane >> 4;
+    const int first = static_cast<int>((row & 1) * Q + (row >> 1) * H);
+    auto field = [&](int i) { return i < N ? value(i) : 0.0; };
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+        const double a = halve<2>(field(q), field(q + H));
+        const double b = halve<2>(field(q + Q), field(q + H + Q));
+        double v = halve<1>(a, b);
+        v += row_rotate<8>(v);
+        v += row_rotate<4>(v);
+        v += row_rotate<2>(v);
+        v += row_rotate<1>(v);
+        if ((lane & 15u) == 0 && first + q < N)
+            out[first + q] = v;
+    }
+}
+
 __device__ __forceinline__ float wave_min(float v)
 {
 #pragma unroll

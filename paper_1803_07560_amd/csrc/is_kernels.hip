@@ -461,12 +461,7 @@ __global__ void __launch_bounds__(BLOCK) is_kernel(IsArgs ia)
                         ? 0.0
                         : exp(static_cast<double>(wave_sigma) - static_cast<double>(sigma)));
         }
-#pragma unroll
-        for (int i = 0; i < NF; ++i) {
-            const double v = dev::wave_sum(acc[i]);
-            if (lane == 0)
-                red[wave][i] = v;
-        }
+        dev::wave_sums<NF>([&](int i) { return acc[i]; }, red[wave], lane);
         if (lane == 0)
             red_sigma[wave] = wave_sigma;
         __syncthreads();

@@ -130,7 +130,10 @@ typedef struct {
 /* Launch shape.  A NULL bfi_launch* takes the tuned (else default) shape for
  * the lattice and precision; in a given struct, samples_per_thread = 0,
  * block = 0 and persistent = -1 each take the tuned value.  Work items hold
- * samples_per_thread * block consecutive samples of one subvolume. */
+ * samples_per_thread * block consecutive samples of one subvolume; where the
+ * caller leaves samples_per_thread open, BFI_FP64 evaluations too small to fill
+ * the chip with such items are cut into smaller ones (the sums differ from the
+ * launch shape's in the order of summation only). */
 typedef struct {
     int32_t samples_per_thread; /* K: samples each thread takes per work item */
     int32_t block;              /* threads per block: 64, 128, 256, 512 or 1024
@@ -206,7 +209,9 @@ bfi_status bfi_eval(bfi_context *ctx, const bfi_lattice *lat, bfi_precision prec
  * parameter block, (count + 1) first-item indices, work items (32 B), item
  * records (BFI_PARTIAL_LEN(nx) doubles each, plus 2d with split statistics),
  * subvolume records (plus BFI_SPLIT_LEN(d) with split statistics), the queue
- * head.  Items hold samples_per_thread * block samples of one subvolume.
+ * head.  Items are bfi_eval's; where they are smaller than the launch shape's
+ * (see bfi_launch) and their layout exceeds the array, the launch shape's
+ * items are taken.
  * Every call on a device shares that device's array: calls that overlap in
  * time on one device (from two threads or two contexts) race.  Errors: those
  * of bfi_eval, and EINVAL (with the bytes needed) when the layout exceeds the

@@ -131,25 +131,40 @@ extern "C" bfi_status bfi_eval_noalloc(bfi_context *ctx, const bfi_lattice *lat,
             return fail(BFI_EINVAL, "block must be 64, 128, 256, 512 or 1024 (got %d)", l.block);
         if (l.samples_per_thread < 1 || l.samples_per_thread > (1 << 20))
             return fail(BFI_EINVAL, "samples_per_thread out of range");
-        const uint64_t chunk = static_cast<uint64_t>(l.samples_per_thread) * l.block;
-        if (chunk > 0x7FFFFFFFull)
+        if (static_cast<uint64_t>(l.samples_per_thread) * l.block > 0x7FFFFFFFull)
             return fail(BFI_EINVAL, "samples per work item exceed 2^31");
-        uint64_t nitems = 0;
-        for (size_t s = 0; s < subs->count; ++s) {
-            nitems += subs->n[s] / chunk + (subs->n[s] % chunk != 0);
-            if (nitems > 0x7FFFFFFFull)
-                return fail(BFI_EINVAL, "more than 2^31 work items; raise samples_per_thread");
-        }
+        BFI_HIP(hipSetDevice(ctx->device));
+        LaunchSpec spec{prec, l.block, split ? 1 : 0, l.persistent, 0, lat->observable,
+                        lat->antithetic};
+        KernelInfo info{};
+        BFI_HIP(kernel_info(lat->nx, lat->nt, spec, &info));
+        const uint64_t resident = static_cast<uint64_t>(std::max(info.blocks_per_cu, 1)) *
+                                  std::max(ctx->cu_count, 1);
         const size_t nsub = subs->count;
         const int rec_len = BFI_PARTIAL_LEN(lat->nx);
-        const Layout L = layout_for(nsub, d, rec_len, nitems, split != nullptr);
+        bool spread = spread_items(prec, launch);
+        uint64_t chunk = 0, nitems = 0;
+        Layout L{};
+        for (;;) {
+            chunk = item_samples(l, spread, subs->n, nsub, resident);
+            nitems = 0;
+            for (size_t s = 0; s < nsub; ++s) {
+                nitems += subs->n[s] / chunk + (subs->n[s] % chunk != 0);
+                if (nitems > 0x7FFFFFFFull)
+                    return fail(BFI_EINVAL, "more than 2^31 work items; raise samples_per_thread");
+            }
+            L = layout_for(nsub, d, rec_len, nitems, split != nullptr);
+            // a list whose shorter items do not fit keeps the launch shape's items
+            if (L.total <= kScratchBytes || !spread)
+                break;
+            spread = false;
+        }
         if (L.total > kScratchBytes)
             return fail(BFI_EINVAL,
                         "the evaluation needs %zu bytes of scratch (%zu subvolumes, %llu work "
                         "items); the allocation-free entry point holds at most %zu",
                         L.total, nsub, static_cast<unsigned long long>(nitems), kScratchBytes);
 
-        BFI_HIP(hipSetDevice(ctx->device));
         hipStream_t st = ctx->stream;
         auto at = [&](size_t off) { return static_cast<void *>(base + off); };
         const size_t nd = nsub * static_cast<size_t>(d);
@@ -184,13 +199,7 @@ extern "C" bfi_status bfi_eval_noalloc(bfi_context *ctx, const bfi_lattice *lat,
                      rec_len};
         BFI_HIP(launch_build_items(ba, st));
 
-        LaunchSpec spec{prec, l.block, split ? 1 : 0, l.persistent, 0, lat->observable,
-                        lat->antithetic};
         if (l.persistent) {
-            KernelInfo info{};
-            BFI_HIP(kernel_info(lat->nx, lat->nt, spec, &info));
-            const uint64_t resident = static_cast<uint64_t>(std::max(info.blocks_per_cu, 1)) *
-                                      std::max(ctx->cu_count, 1);
             spec.grid = static_cast<uint32_t>(std::min<uint64_t>(resident, nitems));
             BFI_HIP(launch_reset_head(head, st));
         } else {

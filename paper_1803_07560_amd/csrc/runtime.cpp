@@ -308,6 +308,52 @@ bfi_launch resolve_launch(const bfi_context *ctx, const bfi_lattice &lat, int pr
     return l;
 }
 
+uint64_t item_samples(const bfi_launch &l, bool spread, const uint64_t *n, size_t nsub,
+                      uint64_t resident)
+{
+    const uint64_t block = static_cast<uint64_t>(l.block);
+    const uint64_t most = static_cast<uint64_t>(l.samples_per_thread) * block;
+    // the resident blocks' rounds of items from which the last one no longer matters
+    constexpr uint64_t kRounds = 8;
+    if (!spread || resident == 0 || nsub > kRounds * resident)
+        return most;
+    uint64_t total = 0;
+    for (size_t s = 0; s < nsub; ++s) {
+        if (n[s] >= kRounds * resident * most)
+            return most;
+        total += n[s];
+    }
+    if (total >= kRounds * resident * most)
+        return most;
+    // in samples per thread: what an item costs beside its samples (the queue,
+    // its parameters, the reduction)
+    constexpr uint64_t kItemCost = 3;
+    uint64_t best = most, best_cost = ~uint64_t(0), last = 0;
+    for (uint64_t k : {1, 2, 3, 4, 6, 8}) {
+        const uint64_t m = std::min<uint64_t>((total + k * resident * block - 1) /
+                                                  (k * resident * block),
+                                              static_cast<uint64_t>(l.samples_per_thread));
+        if (m == last)
+            continue;
+        last = m;
+        const uint64_t chunk = m * block;
+        uint64_t items = 0;
+        for (size_t s = 0; s < nsub; ++s)
+            items += n[s] / chunk + (n[s] % chunk != 0);
+        // two upper bounds of the time of blocks that take the next item as they
+        // go: whole rounds of the longest item, and the shared work plus one item
+        const uint64_t rounds = (items + resident - 1) / resident * (m + kItemCost);
+        const uint64_t shared =
+            (total / block + items * kItemCost + resident - 1) / resident + m + kItemCost;
+        const uint64_t cost = std::min(rounds, shared);
+        if (cost < best_cost) {
+            best_cost = cost;
+            best = chunk;
+        }
+    }
+    return best;
+}
+
 namespace {
 
 // Neumaier-compensated sum.
@@ -579,11 +625,26 @@ bfi_status plan_build_core(bfi_context *ctx, int kind, const bfi_lattice &lat, i
                                 "threads (got %d)", l.block);
     if (l.samples_per_thread < 1 || l.samples_per_thread > (1 << 20))
         return fail(BFI_EINVAL, "samples_per_thread out of range");
-    const uint64_t chunk = static_cast<uint64_t>(l.samples_per_thread) * l.block;
-    if (chunk > 0x7FFFFFFFull)
+    if (static_cast<uint64_t>(l.samples_per_thread) * l.block > 0x7FFFFFFFull)
         return fail(BFI_EINVAL, "samples per work item exceed 2^31");
 
+    // blocks that fill the chip once
+    KernelInfo info{};
+    if (kind == 0 || kind == 2) {
+        LaunchSpec spec{prec, l.block, split ? 1 : 0, 1, 0, lat.observable, lat.antithetic};
+        const hipError_t q = kind == 0 ? kernel_info(lat.nx, lat.nt, spec, &info)
+                                       : is_kernel_info(lat.nx, lat.nt, spec, &info);
+        if (q != hipSuccess)
+            return hip_fail(q, "kernel occupancy query");
+    } else {
+        info.blocks_per_cu = 4;  // 104 VGPRs: 4 waves per SIMD, one block per SIMD
+    }
+    const uint64_t resident = static_cast<uint64_t>(std::max(info.blocks_per_cu, 1)) *
+                              std::max(ctx->cu_count, 1);
+
     // work items: ceil(n / chunk) per subvolume, subvolumes in list order
+    const uint64_t chunk = item_samples(l, spread_items(prec, launch), subs.n.data(), subs.size(),
+                                        resident);
     std::vector<WorkItem> items;
     std::vector<uint32_t> first(subs.size() + 1, 0);
     uint64_t total_items = 0, n_evals = 0;
@@ -690,21 +751,8 @@ bfi_status plan_build_core(bfi_context *ctx, int kind, const bfi_lattice &lat, i
     if (e != hipSuccess)
         return cleanup_fail("hipEventCreate");
 
-    // persistent launches fill the chip once: resident blocks per CU x CUs
+    // persistent launches fill the chip once
     if (l.persistent) {
-        KernelInfo info{};
-        if (kind == 0 || kind == 2) {
-            LaunchSpec spec{prec, l.block, split ? 1 : 0, 1, 0, lat.observable,
-                            lat.antithetic};
-            e = kind == 0 ? kernel_info(lat.nx, lat.nt, spec, &info)
-                          : is_kernel_info(lat.nx, lat.nt, spec, &info);
-            if (e != hipSuccess)
-                return cleanup_fail("kernel occupancy query");
-        } else {
-            info.blocks_per_cu = 4;  // 104 VGPRs: 4 waves per SIMD, one block per SIMD
-        }
-        const uint64_t resident = static_cast<uint64_t>(std::max(info.blocks_per_cu, 1)) *
-                                  std::max(ctx->cu_count, 1);
         p->grid = static_cast<uint32_t>(std::min<uint64_t>(resident, items.size()));
     } else {
         p->grid = static_cast<uint32_t>(items.size());

@@ -139,6 +139,31 @@ struct TracePhases {
 bfi_launch resolve_launch(const bfi_context *ctx, const bfi_lattice &lat, int prec, bool split,
                           const bfi_launch *req);
 
+// Whether an evaluation's work items may be made smaller than its launch shape
+// says, to fill the chip: the caller left samples_per_thread open, and the form
+// is plain FP64.  The shifted forms keep the launch shape's items at every
+// size: a thread's shift is set by the samples that it takes, and with it the
+// rounding of their weights (in FP32) and the scale of the record.
+inline bool spread_items(int prec, const bfi_launch *req)
+{
+    return prec == kFP64 && !(req && req->samples_per_thread > 0);
+}
+// Samples per work item of a list of sample counts, at most the launch shape's
+// samples_per_thread x block.  The tuned shapes are those of long runs, whose
+// items hold 2^16 samples and more; a list of fewer than eight rounds of such
+// items over the `resident` blocks leaves blocks without work (2^6 subvolumes
+// of 46875 samples made 64 items for 512 blocks) and ends on a round that is
+// partly empty.  With `spread`, such a list is cut into about one to eight
+// rounds of shorter items, as many as a bound of the finishing time prefers.
+// Measured, launch shape's items -> these, whole calls: 10x2 FP64, 3e6
+// evaluations over 64 subvolumes 416 -> 291 us; 301 uneven leaves of 2^10 ..
+// 2^17 samples with split statistics 925 -> 501 us; spherical sampler, 2^24
+// over 64 shells in two passes 2.16 -> 1.60 ms.  From eight rounds on the
+// launch shape's items are as fast and there are fewer records to merge (2^30
+// evaluations of 10x2: the same 4096 items, 11.8 ms).
+uint64_t item_samples(const bfi_launch &l, bool spread, const uint64_t *n, size_t nsub,
+                      uint64_t resident);
+
 // Host finalize of partial records (see bfi_finalize).
 // evals_per_sample: integrand evaluations behind one record sample (2 for
 // antithetic pairs), for n_evals.  leaf_var (nsub doubles, or NULL) gets each

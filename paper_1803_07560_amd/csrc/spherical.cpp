@@ -105,7 +105,12 @@ bfi_status sph_eval(bfi_context *ctx, const bfi_lattice &lat, int prec, uint64_t
         return fail(BFI_EINVAL, "block must be 64, 128 or 256 (got %d)", l.block);
     if (l.samples_per_thread < 1 || l.samples_per_thread > (1 << 20))
         return fail(BFI_EINVAL, "samples_per_thread out of range");
-    const uint64_t chunk = static_cast<uint64_t>(l.samples_per_thread) * l.block;
+    LaunchSpec spec{prec, l.block, 0, l.persistent, 0, lat.observable, 0};
+    KernelInfo info{};
+    BFI_HIP(sph_kernel_info(lat.nx, lat.nt, spec, &info));
+    const uint64_t resident = static_cast<uint64_t>(std::max(info.blocks_per_cu, 1)) *
+                              std::max(ctx->cu_count, 1);
+    const uint64_t chunk = item_samples(l, spread_items(prec, launch), sh.n, ns, resident);
     std::vector<WorkItem> items;
     std::vector<uint32_t> first(ns + 1);
     for (size_t s = 0; s < ns; ++s) {
@@ -162,14 +167,9 @@ bfi_status sph_eval(bfi_context *ctx, const bfi_lattice &lat, int prec, uint64_t
                            hipMemcpyHostToDevice, st));
     BFI_HIP(hipMemcpyAsync(base + o_first, first.data(), (ns + 1) * 4, hipMemcpyHostToDevice, st));
 
-    LaunchSpec spec{prec, l.block, 0, l.persistent, 0, lat.observable, 0};
     auto *head = reinterpret_cast<uint32_t *>(base + o_head);
     if (l.persistent) {
-        KernelInfo info{};
-        BFI_HIP(sph_kernel_info(lat.nx, lat.nt, spec, &info));
-        spec.grid = static_cast<uint32_t>(std::min<uint64_t>(
-            static_cast<uint64_t>(std::max(info.blocks_per_cu, 1)) * std::max(ctx->cu_count, 1),
-            items.size()));
+        spec.grid = static_cast<uint32_t>(std::min<uint64_t>(resident, items.size()));
         BFI_HIP(launch_reset_head(head, st));
     } else {
         spec.grid = static_cast<uint32_t>(items.size());

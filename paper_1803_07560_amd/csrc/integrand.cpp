@@ -46,35 +46,16 @@ bfi_status check_integrand(const bfi_integrand *f, int *d)
 
 // Records and split statistics of a subvolume list for an integrand.
 bfi_status eval_records(bfi_context *ctx, const bfi_integrand &f, int d, uint64_t seed,
-                        const SubList &subs, const bfi_launch *launch, std::vector<double> *rec,
-                        std::vector<double> *split, int *rec_len)
+                        const bfi_subvolumes &subs, const bfi_launch *launch,
+                        std::vector<double> *rec, std::vector<double> *split, int *rec_len)
 {
-    if (f.kind == BFI_INTEGRAND_NSPHERE) {
-        bfi_plan *p = nullptr;
-        BFI_TRY(plan_build_nsphere(ctx, d, subs, launch, &p));
-        p->launch.use_graph = 0;
-        *rec_len = p->rec_len;
-        rec->assign(subs.size() * p->rec_len, 0.0);
-        split->assign(subs.size() * BFI_SPLIT_LEN(d), 0.0);
-        bfi_status s = plan_enqueue(p, seed, nullptr, ctx->stream, false);
-        p->last_stream = ctx->stream;
-        if (s == BFI_OK)
-            s = bfi_plan_partials(p, rec->data());
-        if (s == BFI_OK) {
-            hipError_t e = hipMemcpy(split->data(), p->d_sub_split, split->size() * sizeof(double),
-                                     hipMemcpyDeviceToHost);
-            if (e != hipSuccess)
-                s = hip_fail(e, "hipMemcpy(split)");
-        }
-        plan_free(p);
-        return s;
-    }
-    *rec_len = BFI_PARTIAL_LEN(f.lat.nx);
-    rec->assign(subs.size() * *rec_len, 0.0);
-    split->assign(subs.size() * BFI_SPLIT_LEN(d), 0.0);
-    bfi_subvolumes v = subs.view();
-    return bfi_eval(ctx, &f.lat, static_cast<bfi_precision>(f.prec), seed, &v, launch, rec->data(),
-                    split->data());
+    *rec_len = BFI_PARTIAL_LEN(f.kind == BFI_INTEGRAND_NSPHERE ? 0 : f.lat.nx);
+    rec->assign(subs.count * *rec_len, 0.0);
+    split->assign(subs.count * BFI_SPLIT_LEN(d), 0.0);
+    if (f.kind == BFI_INTEGRAND_NSPHERE)
+        return eval_once_nsphere(ctx, d, seed, subs, launch, rec->data(), split->data());
+    return bfi_eval(ctx, &f.lat, static_cast<bfi_precision>(f.prec), seed, &subs, launch,
+                    rec->data(), split->data());
 }
 
 struct Estimate {
@@ -160,12 +141,11 @@ bfi_status bfi_integrand_eval(bfi_context *ctx, const bfi_integrand *f, uint64_t
         }
         BFI_TRY(check_subvolumes(&shape, subs));
         BFI_HIP(hipSetDevice(ctx->device));
-        const SubList list = SubList::copy_of(*subs, d);
         std::vector<double> rec, spl;
         int rec_len = 0;
-        BFI_TRY(eval_records(ctx, *f, d, seed, list, launch, &rec, &spl, &rec_len));
-        for (size_t s = 0; s < list.size(); ++s) {
-            const Estimate e = estimate(*f, d, &list.lo[s * d], &list.hi[s * d], &rec[s * rec_len],
+        BFI_TRY(eval_records(ctx, *f, d, seed, *subs, launch, &rec, &spl, &rec_len));
+        for (size_t s = 0; s < subs->count; ++s) {
+            const Estimate e = estimate(*f, d, &subs->lo[s * d], &subs->hi[s * d], &rec[s * rec_len],
                                         &spl[s * BFI_SPLIT_LEN(d)]);
             result[s] = e.result;
             abserr[s] = e.abserr;
@@ -222,7 +202,7 @@ bfi_status bfi_integrate_hdi(bfi_context *ctx, const bfi_integrand *f, uint64_t 
                 }
             std::vector<double> rec, spl;
             int rec_len = 0;
-            BFI_TRY(eval_records(ctx, *f, d, seed, work, launch, &rec, &spl, &rec_len));
+            BFI_TRY(eval_records(ctx, *f, d, seed, work.view(), launch, &rec, &spl, &rec_len));
             evals += open.size() * per_sub;
             ++generations;
 

@@ -144,14 +144,6 @@ hipError_t launch_debug_action(int nx, int nt, const DebugActionArgs &args, hipS
     return hipErrorNotSupported;
 }
 
-template <class T>
-T *dev_alloc(size_t count, hipError_t *err)
-{
-    void *p = nullptr;
-    *err = count ? hipMalloc(&p, count * sizeof(T)) : hipSuccess;
-    return static_cast<T *>(p);
-}
-
 // Device buffers freed on scope exit (for the one-shot test hooks).
 struct DevBuf {
     void *p = nullptr;
@@ -227,18 +219,6 @@ ActionCoef make_coef(const bfi_lattice &lat)
     c.inv_2Dtau = 1.0 / (2.0 * lat.D * lat.tau);
     c.half_m2 = 0.5 * lat.m2;
     return c;
-}
-
-SubList SubList::copy_of(const bfi_subvolumes &s, int d)
-{
-    SubList out;
-    out.d = d;
-    out.id.assign(s.id, s.id + s.count);
-    out.n.assign(s.n, s.n + s.count);
-    out.offset.assign(s.offset, s.offset + s.count);
-    out.lo.assign(s.lo, s.lo + s.count * d);
-    out.hi.assign(s.hi, s.hi + s.count * d);
-    return out;
 }
 
 SubList uniform_split(int d, const double *box_lo, const double *box_hi, int k, uint64_t budget)
@@ -528,73 +508,135 @@ bfi_status plan_free(bfi_plan *p)
         (void)hipEventDestroy(p->ev_start);
     if (p->ev_stop)
         (void)hipEventDestroy(p->ev_stop);
-    void *bufs[] = {p->d_base64, p->d_scale64, p->d_base32, p->d_scale32, p->d_ids,
-                    p->d_offsets, p->d_params, p->d_items, p->d_item_rec, p->d_item_split, p->d_sub_first,
-                    p->d_sub_rec, p->d_sub_split, p->d_head, p->d_is_table};
-    for (void *b : bufs)
-        if (b)
-            (void)hipFree(b);
+    if (p->d_block)
+        (void)hipFree(p->d_block);
     delete p;
     return BFI_OK;
 }
 
-namespace {
-
-bfi_status plan_build_core(bfi_context *ctx, int kind, const bfi_lattice &lat, int d, int nx,
-                           int prec, const SubList &subs, const bfi_launch *launch, bool split,
-                           bfi_plan **out);
-
-}  // namespace
-
-bfi_status plan_build(bfi_context *ctx, const bfi_lattice &lat, int prec, const SubList &subs,
-                      const bfi_launch *launch, bool split, bfi_plan **out)
+CallScratch::~CallScratch()
 {
-    return plan_build_core(ctx, 0, lat, lat.nx * lat.nt, lat.nx, prec, subs, launch, split, out);
+    if (ctx_ && queued_)
+        (void)hipStreamSynchronize(ctx_->stream);
+    if (own_dev_)
+        (void)hipFree(own_dev_);
 }
 
-bfi_status plan_build_nsphere(bfi_context *ctx, int dim, const SubList &subs,
-                              const bfi_launch *launch, bfi_plan **out)
+bfi_status CallScratch::take(bfi_context *ctx, size_t host_bytes, size_t dev_bytes)
 {
-    if (dim < 1 || dim > kMaxNsphereDim)
-        return fail(BFI_EINVAL, "N-sphere dimension must be in [1, %d]", kMaxNsphereDim);
-    bfi_lattice none{};
-    none.nx = 0;
-    none.nt = 1;
-    return plan_build_core(ctx, 1, none, dim, 0, kFP64, subs, launch, true, out);
-}
-
-bfi_status plan_build_is(bfi_context *ctx, const bfi_lattice &lat, int prec,
-                         const SubList &streams, const IsTable &table, const bfi_launch *launch,
-                         bfi_plan **out)
-{
-    if (lat.nx * lat.nt > kIsMaxD)
-        return fail(BFI_EUNSUPPORTED, "the Gaussian-proposal sampler is compiled for d <= %d",
-                    kIsMaxD);
-    bfi_plan *p = nullptr;
-    BFI_TRY(plan_build_core(ctx, 2, lat, lat.nx * lat.nt, lat.nx, prec, streams, launch, false,
-                            &p));
-    hipError_t e = hipMalloc(reinterpret_cast<void **>(&p->d_is_table), sizeof(IsTable));
-    if (e == hipSuccess)
-        e = hipMemcpy(p->d_is_table, &table, sizeof(IsTable), hipMemcpyHostToDevice);
-    if (e != hipSuccess) {
-        plan_free(p);
-        return hip_fail(e, "sampler table upload");
+    ctx_ = ctx;
+    if (std::max(host_bytes, dev_bytes) <= kScratchLimit)
+        held_ = std::unique_lock<std::mutex>(ctx->scratch_busy, std::try_to_lock);
+    if (!held_.owns_lock()) {
+        own_host_.resize(host_bytes);
+        BFI_HIP(hipMalloc(reinterpret_cast<void **>(&own_dev_), dev_bytes));
+        host_ = own_host_.data();
+        dev_ = own_dev_;
+        return BFI_OK;
     }
-    *out = p;
+    constexpr size_t kLeast = size_t(1) << 20;
+    auto grown = [&](size_t need, size_t cap) {
+        return std::min(std::max({need, 2 * cap, kLeast}), kScratchLimit);
+    };
+    if (dev_bytes > ctx->scratch_dev_cap) {
+        if (ctx->scratch_dev)
+            BFI_HIP(hipFree(ctx->scratch_dev));
+        const size_t cap = grown(dev_bytes, ctx->scratch_dev_cap);
+        ctx->scratch_dev = nullptr;
+        ctx->scratch_dev_cap = 0;
+        BFI_HIP(hipMalloc(reinterpret_cast<void **>(&ctx->scratch_dev), cap));
+        ctx->scratch_dev_cap = cap;
+    }
+    if (host_bytes > ctx->scratch_host_cap) {
+        if (ctx->scratch_host)
+            BFI_HIP(hipHostFree(ctx->scratch_host));
+        const size_t cap = grown(host_bytes, ctx->scratch_host_cap);
+        ctx->scratch_host = nullptr;
+        ctx->scratch_host_cap = 0;
+        BFI_HIP(hipHostMalloc(reinterpret_cast<void **>(&ctx->scratch_host), cap,
+                              hipHostMallocDefault));
+        ctx->scratch_host_cap = cap;
+    }
+    host_ = ctx->scratch_host;
+    dev_ = ctx->scratch_dev;
+    return BFI_OK;
+}
+
+bfi_status CallScratch::upload(size_t bytes)
+{
+    queued_ = true;
+    BFI_HIP(hipMemcpyAsync(dev_, host_, bytes, hipMemcpyHostToDevice, ctx_->stream));
+    return BFI_OK;
+}
+
+bfi_status CallScratch::download(size_t from, size_t bytes)
+{
+    BFI_HIP(hipMemcpyAsync(host_, dev_ + from, bytes, hipMemcpyDeviceToHost, ctx_->stream));
+    BFI_HIP(hipStreamSynchronize(ctx_->stream));
+    queued_ = false;
+    return BFI_OK;
+}
+
+bfi_status resident_blocks(bfi_context *ctx, int kind, const bfi_lattice &lat,
+                           const LaunchSpec &spec, uint64_t *blocks)
+{
+    const std::array<int, 8> key{kind,       lat.nx,     lat.nt,   spec.prec,
+                                 spec.block, spec.split, spec.obs, spec.pair};
+    int per_cu = 0;
+    {
+        std::lock_guard<std::mutex> lock(ctx->occupancy_mutex);
+        const auto it = ctx->occupancy.find(key);
+        if (it != ctx->occupancy.end())
+            per_cu = it->second;
+    }
+    if (per_cu == 0) {
+        KernelInfo info{};
+        hipError_t e = hipSuccess;
+        if (kind == 0)
+            e = kernel_info(lat.nx, lat.nt, spec, &info);
+        else if (kind == 2)
+            e = is_kernel_info(lat.nx, lat.nt, spec, &info);
+        else if (kind == 3)
+            e = sph_kernel_info(lat.nx, lat.nt, spec, &info);
+        else
+            info.blocks_per_cu = 4;  // 104 VGPRs: 4 waves per SIMD, one block per SIMD
+        if (e != hipSuccess)
+            return hip_fail(e, "kernel occupancy query");
+        per_cu = std::max(info.blocks_per_cu, 1);
+        std::lock_guard<std::mutex> lock(ctx->occupancy_mutex);
+        ctx->occupancy[key] = per_cu;
+    }
+    *blocks = static_cast<uint64_t>(per_cu) * std::max(ctx->cu_count, 1);
     return BFI_OK;
 }
 
 namespace {
 
-bfi_status plan_build_core(bfi_context *ctx, int kind, const bfi_lattice &lat, int d, int nx,
-                           int prec, const SubList &subs, const bfi_launch *launch, bool split,
-                           bfi_plan **out)
+// What is evaluated: a plan (scratch NULL) or one call's list, whose memory the
+// call lends.
+struct PlanSpec {
+    int kind;
+    bfi_lattice lat;
+    int d, nx, prec;
+    bool split;
+    uint64_t seed;
+    const bfi_launch *launch;
+    const IsTable *table;  // kind 2
+};
+
+bfi_status plan_build_core(bfi_context *ctx, const PlanSpec &what, const bfi_subvolumes &subs,
+                           CallScratch *scratch, bfi_plan **out)
 {
+    const int kind = what.kind, d = what.d, prec = what.prec;
+    const bfi_lattice &lat = what.lat;
+    const bfi_launch *launch = what.launch;
+    const bool split = what.split;
+    const size_t nsub = subs.count;
     if (kind == 0 && split && d > 32)
         return fail(BFI_EUNSUPPORTED, "split statistics need d <= 32 (d = %d)", d);
-    if (subs.size() == 0)
+    if (nsub == 0)
         return fail(BFI_EINVAL, "empty subvolume list");
-    if (subs.size() > 0xFFFFFFFFull)
+    if (nsub > 0xFFFFFFFFull)
         return fail(BFI_EINVAL, "too many subvolumes");
     // the tuned table holds mc_kernel shapes; the Gaussian-proposal sampler's
     // kernel (more work per sample) keeps 256 samples per thread and 256-thread
@@ -627,141 +669,222 @@ bfi_status plan_build_core(bfi_context *ctx, int kind, const bfi_lattice &lat, i
         return fail(BFI_EINVAL, "samples_per_thread out of range");
     if (static_cast<uint64_t>(l.samples_per_thread) * l.block > 0x7FFFFFFFull)
         return fail(BFI_EINVAL, "samples per work item exceed 2^31");
-
-    // blocks that fill the chip once
-    KernelInfo info{};
-    if (kind == 0 || kind == 2) {
-        LaunchSpec spec{prec, l.block, split ? 1 : 0, 1, 0, lat.observable, lat.antithetic};
-        const hipError_t q = kind == 0 ? kernel_info(lat.nx, lat.nt, spec, &info)
-                                       : is_kernel_info(lat.nx, lat.nt, spec, &info);
-        if (q != hipSuccess)
-            return hip_fail(q, "kernel occupancy query");
-    } else {
-        info.blocks_per_cu = 4;  // 104 VGPRs: 4 waves per SIMD, one block per SIMD
-    }
-    const uint64_t resident = static_cast<uint64_t>(std::max(info.blocks_per_cu, 1)) *
-                              std::max(ctx->cu_count, 1);
+    uint64_t resident = 0;
+    BFI_TRY(resident_blocks(ctx, kind, lat,
+                            LaunchSpec{prec, l.block, split ? 1 : 0, 1, 0, lat.observable,
+                                       lat.antithetic},
+                            &resident));
 
     // work items: ceil(n / chunk) per subvolume, subvolumes in list order
-    const uint64_t chunk = item_samples(l, spread_items(prec, launch), subs.n.data(), subs.size(),
-                                        resident);
-    std::vector<WorkItem> items;
-    std::vector<uint32_t> first(subs.size() + 1, 0);
-    uint64_t total_items = 0, n_evals = 0;
-    for (size_t s = 0; s < subs.size(); ++s) {
+    const uint64_t chunk = item_samples(l, spread_items(prec, launch), subs.n, nsub, resident);
+    uint64_t nitems = 0, n_evals = 0;
+    for (size_t s = 0; s < nsub; ++s) {
         // checked per subvolume, so the running count cannot wrap
-        total_items += subs.n[s] / chunk + (subs.n[s] % chunk != 0);
-        if (total_items > 0x7FFFFFFFull)
+        nitems += subs.n[s] / chunk + (subs.n[s] % chunk != 0);
+        if (nitems > 0x7FFFFFFFull)
             return fail(BFI_EINVAL, "more than 2^31 work items; raise samples_per_thread");
-    }
-    items.reserve(total_items);
-    for (size_t s = 0; s < subs.size(); ++s) {
-        first[s] = static_cast<uint32_t>(items.size());
-        for (uint64_t start = 0; start < subs.n[s]; start += chunk) {
-            const uint64_t cnt = std::min<uint64_t>(chunk, subs.n[s] - start);
-            items.push_back(WorkItem{nullptr, nullptr, start, static_cast<uint32_t>(s),
-                                     static_cast<uint32_t>(cnt)});
-        }
         n_evals += subs.n[s];
     }
     if (lat.antithetic)
         n_evals *= 2;  // two points per sample index
-    first[subs.size()] = static_cast<uint32_t>(items.size());
 
-    // point map descriptors: scale = (hi - lo) 2^-32, base = lo + scale/2
-    const size_t nd = subs.size() * d;
-    std::vector<double> base64(nd), scale64(nd);
-    std::vector<float> base32(nd), scale32(nd);
-    for (size_t i = 0; i < nd; ++i) {
-        scale64[i] = (subs.hi[i] - subs.lo[i]) * 0x1p-32;
-        base64[i] = subs.lo[i] + 0.5 * scale64[i];
-        scale32[i] = static_cast<float>(scale64[i]);
-        base32[i] = static_cast<float>(base64[i]);
-    }
+    // one device block: what the host writes first (one image), then the records
+    const int rec_len = BFI_PARTIAL_LEN(what.nx);
+    const size_t split_len = BFI_SPLIT_LEN(d);
+    size_t at = 0;
+    auto region = [&](size_t bytes) {
+        const size_t here = at;
+        at += (bytes + 255) & ~size_t(255);
+        return here;
+    };
+    // the point map in the precision that the kernel reads (the
+    // Gaussian-proposal sampler has its own)
+    const size_t real = prec == kFP32Shifted ? sizeof(float) : sizeof(double);
+    const size_t map_bytes = kind == 2 ? 0 : nsub * d * real;
+    const size_t o_params = region(sizeof(EvalParams)), o_head = region(sizeof(uint32_t)),
+                 o_table = region(kind == 2 ? sizeof(IsTable) : 0), o_base = region(map_bytes),
+                 o_scale = region(map_bytes), o_ids = region(nsub * 8),
+                 o_offsets = region(nsub * 8), o_first = region((nsub + 1) * 4),
+                 o_items = region(nitems * sizeof(WorkItem));
+    const size_t image = at;
+    const size_t o_sub_rec = region(nsub * rec_len * 8),
+                 o_sub_split = region(split ? nsub * split_len * 8 : 0);
+    const size_t records = at - image;
+    const size_t o_item_rec = region(nitems * rec_len * 8),
+                 o_item_split = region(split ? nitems * 2 * d * 8 : 0);
 
+    std::vector<char> own_image;
     auto *p = new bfi_plan();
+    struct Guard {
+        bfi_plan *p;
+        ~Guard()
+        {
+            if (p)
+                plan_free(p);
+        }
+    } guard{p};
+    char *img = nullptr, *dev = nullptr;
+    if (scratch) {
+        BFI_TRY(scratch->take(ctx, std::max(image, records), at));
+        img = scratch->host();
+        dev = scratch->dev();
+    } else {
+        own_image.resize(image);
+        img = own_image.data();
+        BFI_HIP(hipMalloc(reinterpret_cast<void **>(&p->d_block), at));
+        dev = p->d_block;
+    }
     p->ctx = ctx;
     p->kind = kind;
     p->lat = lat;
     p->prec = prec;
     p->d = d;
-    p->nx = nx;
-    p->rec_len = BFI_PARTIAL_LEN(nx);
+    p->nx = what.nx;
+    p->rec_len = rec_len;
     p->split = split;
-    p->subs = subs;
+    p->nsub = nsub;
     p->launch = l;
-    p->nitems = static_cast<uint32_t>(items.size());
+    p->nitems = static_cast<uint32_t>(nitems);
     p->n_evals = n_evals;
-
-    hipError_t e = hipSuccess;
-    auto cleanup_fail = [&](const char *what) {
-        bfi_status st = hip_fail(e, what);
-        plan_free(p);
-        return st;
-    };
-#define BFI_ALLOC(field, T, count)                                  \
-    do {                                                            \
-        p->field = dev_alloc<T>((count), &e);                       \
-        if (e != hipSuccess)                                        \
-            return cleanup_fail("hipMalloc(" #field ")");           \
-    } while (0)
-    BFI_ALLOC(d_base64, double, nd);
-    BFI_ALLOC(d_scale64, double, nd);
-    BFI_ALLOC(d_base32, float, nd);
-    BFI_ALLOC(d_scale32, float, nd);
-    BFI_ALLOC(d_ids, uint64_t, subs.size());
-    BFI_ALLOC(d_offsets, uint64_t, subs.size());
-    BFI_ALLOC(d_params, EvalParams, 1);
-    BFI_ALLOC(d_items, WorkItem, items.size());
-    BFI_ALLOC(d_item_rec, double, items.size() * p->rec_len);
-    BFI_ALLOC(d_sub_first, uint32_t, first.size());
-    BFI_ALLOC(d_sub_rec, double, subs.size() * p->rec_len);
-    BFI_ALLOC(d_head, uint32_t, 1);
+    p->d_params = reinterpret_cast<EvalParams *>(dev + o_params);
+    p->d_head = reinterpret_cast<uint32_t *>(dev + o_head);
+    p->d_is_table = kind == 2 ? reinterpret_cast<IsTable *>(dev + o_table) : nullptr;
+    p->d_items = reinterpret_cast<WorkItem *>(dev + o_items);
+    p->d_sub_first = reinterpret_cast<uint32_t *>(dev + o_first);
+    p->d_sub_rec = reinterpret_cast<double *>(dev + o_sub_rec);
+    p->d_item_rec = reinterpret_cast<double *>(dev + o_item_rec);
     if (split) {
-        BFI_ALLOC(d_item_split, double, items.size() * 2 * d);
-        BFI_ALLOC(d_sub_split, double, subs.size() * BFI_SPLIT_LEN(d));
+        p->d_sub_split = reinterpret_cast<double *>(dev + o_sub_split);
+        p->d_item_split = reinterpret_cast<double *>(dev + o_item_split);
     }
-#undef BFI_ALLOC
-    for (size_t i = 0; i < items.size(); ++i) {
-        items[i].params = p->d_params;
-        items[i].rec = p->d_item_rec + i * p->rec_len;
-    }
-    p->params = EvalParams{p->d_base64, p->d_scale64, p->d_base32, p->d_scale32, p->d_ids,
-                           p->d_offsets, kind != 1 ? make_coef(lat) : ActionCoef{}, 0u, 0u};
-    struct Up {
-        void *dst;
-        const void *src;
-        size_t bytes;
-    } ups[] = {{p->d_base64, base64.data(), nd * 8}, {p->d_scale64, scale64.data(), nd * 8},
-               {p->d_base32, base32.data(), nd * 4}, {p->d_scale32, scale32.data(), nd * 4},
-               {p->d_ids, subs.id.data(), subs.size() * 8},
-               {p->d_offsets, subs.offset.data(), subs.size() * 8},
-               {p->d_items, items.data(), items.size() * sizeof(WorkItem)},
-               {p->d_sub_first, first.data(), first.size() * 4},
-               {p->d_params, &p->params, sizeof(EvalParams)}};
-    for (const Up &u : ups) {
-        e = hipMemcpy(u.dst, u.src, u.bytes, hipMemcpyHostToDevice);
-        if (e != hipSuccess)
-            return cleanup_fail("hipMemcpy(plan upload)");
-    }
+    p->params.ids = reinterpret_cast<const uint64_t *>(dev + o_ids);
+    p->params.offsets = reinterpret_cast<const uint64_t *>(dev + o_offsets);
+    p->params.coef = kind != 1 ? make_coef(lat) : ActionCoef{};
+    p->params.seed_lo = static_cast<uint32_t>(what.seed);
+    p->params.seed_hi = static_cast<uint32_t>(what.seed >> 32);
 
-    e = hipEventCreate(&p->ev_start);
-    if (e == hipSuccess)
-        e = hipEventCreate(&p->ev_stop);
-    if (e != hipSuccess)
-        return cleanup_fail("hipEventCreate");
-
-    // persistent launches fill the chip once
-    if (l.persistent) {
-        p->grid = static_cast<uint32_t>(std::min<uint64_t>(resident, items.size()));
+    // point map descriptors: scale = (hi - lo) 2^-32, base = lo + scale/2
+    const size_t nd = kind == 2 ? 0 : nsub * d;
+    if (prec == kFP32Shifted) {
+        auto *base = reinterpret_cast<float *>(img + o_base),
+             *scale = reinterpret_cast<float *>(img + o_scale);
+        p->params.base32 = reinterpret_cast<const float *>(dev + o_base);
+        p->params.scale32 = reinterpret_cast<const float *>(dev + o_scale);
+        for (size_t i = 0; i < nd; ++i) {
+            const double w = (subs.hi[i] - subs.lo[i]) * 0x1p-32;
+            scale[i] = static_cast<float>(w);
+            base[i] = static_cast<float>(subs.lo[i] + 0.5 * w);
+        }
     } else {
-        p->grid = static_cast<uint32_t>(items.size());
+        auto *base = reinterpret_cast<double *>(img + o_base),
+             *scale = reinterpret_cast<double *>(img + o_scale);
+        p->params.base64 = reinterpret_cast<const double *>(dev + o_base);
+        p->params.scale64 = reinterpret_cast<const double *>(dev + o_scale);
+        for (size_t i = 0; i < nd; ++i) {
+            scale[i] = (subs.hi[i] - subs.lo[i]) * 0x1p-32;
+            base[i] = subs.lo[i] + 0.5 * scale[i];
+        }
     }
+    std::memcpy(img + o_params, &p->params, sizeof(EvalParams));
+    std::memset(img + o_head, 0, sizeof(uint32_t));
+    if (kind == 2)
+        std::memcpy(img + o_table, what.table, sizeof(IsTable));
+    std::memcpy(img + o_ids, subs.id, nsub * 8);
+    std::memcpy(img + o_offsets, subs.offset, nsub * 8);
+    auto *first = reinterpret_cast<uint32_t *>(img + o_first);
+    auto *items = reinterpret_cast<WorkItem *>(img + o_items);
+    uint32_t it = 0;
+    for (size_t s = 0; s < nsub; ++s) {
+        first[s] = it;
+        for (uint64_t start = 0; start < subs.n[s]; start += chunk, ++it)
+            items[it] = WorkItem{p->d_params, p->d_item_rec + static_cast<size_t>(it) * rec_len,
+                                 start, static_cast<uint32_t>(s),
+                                 static_cast<uint32_t>(std::min<uint64_t>(chunk, subs.n[s] - start))};
+    }
+    first[nsub] = it;
+    if (scratch) {
+        BFI_TRY(scratch->upload(image));
+    } else {
+        BFI_HIP(hipMemcpy(dev, img, image, hipMemcpyHostToDevice));
+        BFI_HIP(hipEventCreate(&p->ev_start));
+        BFI_HIP(hipEventCreate(&p->ev_stop));
+    }
+    // persistent launches fill the chip once
+    p->grid = static_cast<uint32_t>(l.persistent ? std::min<uint64_t>(resident, nitems) : nitems);
+    guard.p = nullptr;
     *out = p;
     return BFI_OK;
 }
 
+bfi_status run_once(bfi_context *ctx, const PlanSpec &what, const bfi_subvolumes &subs,
+                    double *partials, double *split)
+{
+    CallScratch scratch;
+    bfi_plan *p = nullptr;
+    {
+        TraceRange tb("evaluation: build and upload");
+        BFI_TRY(plan_build_core(ctx, what, subs, &scratch, &p));
+    }
+    const size_t rec_bytes = p->nsub * p->rec_len * sizeof(double);
+    const size_t from = static_cast<size_t>(reinterpret_cast<char *>(p->d_sub_rec) - scratch.dev());
+    const size_t split_bytes = split ? p->nsub * BFI_SPLIT_LEN(p->d) * sizeof(double) : 0;
+    const size_t split_at =
+        split ? static_cast<size_t>(reinterpret_cast<char *>(p->d_sub_split) - scratch.dev()) - from
+              : 0;
+    bfi_status s = plan_enqueue(p, what.seed, nullptr, ctx->stream, false);
+    plan_free(p);
+    BFI_TRY(s);
+    BFI_TRY(scratch.download(from, split ? split_at + split_bytes : rec_bytes));
+    std::memcpy(partials, scratch.host(), rec_bytes);
+    if (split)
+        std::memcpy(split, scratch.host() + split_at, split_bytes);
+    return BFI_OK;
+}
+
 }  // namespace
+
+bfi_status plan_build(bfi_context *ctx, const bfi_lattice &lat, int prec,
+                      const bfi_subvolumes &subs, const bfi_launch *launch, bfi_plan **out)
+{
+    return plan_build_core(ctx,
+                           PlanSpec{0, lat, lat.nx * lat.nt, lat.nx, prec, false, 0, launch,
+                                    nullptr},
+                           subs, nullptr, out);
+}
+
+bfi_status eval_once(bfi_context *ctx, const bfi_lattice &lat, int prec, uint64_t seed,
+                     const bfi_subvolumes &subs, const bfi_launch *launch, double *partials,
+                     double *split)
+{
+    return run_once(ctx,
+                    PlanSpec{0, lat, lat.nx * lat.nt, lat.nx, prec, split != nullptr, seed, launch,
+                             nullptr},
+                    subs, partials, split);
+}
+
+bfi_status eval_once_nsphere(bfi_context *ctx, int dim, uint64_t seed, const bfi_subvolumes &subs,
+                             const bfi_launch *launch, double *partials, double *split)
+{
+    if (dim < 1 || dim > kMaxNsphereDim)
+        return fail(BFI_EINVAL, "N-sphere dimension must be in [1, %d]", kMaxNsphereDim);
+    bfi_lattice none{};
+    none.nx = 0;
+    none.nt = 1;
+    return run_once(ctx, PlanSpec{1, none, dim, 0, kFP64, true, seed, launch, nullptr}, subs,
+                    partials, split);
+}
+
+bfi_status eval_once_is(bfi_context *ctx, const bfi_lattice &lat, int prec, uint64_t seed,
+                        const bfi_subvolumes &streams, const IsTable &table,
+                        const bfi_launch *launch, double *partials)
+{
+    if (lat.nx * lat.nt > kIsMaxD)
+        return fail(BFI_EUNSUPPORTED, "the Gaussian-proposal sampler is compiled for d <= %d",
+                    kIsMaxD);
+    return run_once(ctx,
+                    PlanSpec{2, lat, lat.nx * lat.nt, lat.nx, prec, false, seed, launch, &table},
+                    streams, partials, nullptr);
+}
 
 bfi_status plan_set_seed(bfi_plan *p, uint64_t seed)
 {
@@ -788,7 +911,8 @@ bfi_status plan_enqueue(bfi_plan *p, uint64_t seed, double *dst, hipStream_t st,
     a.samples_per_thread = static_cast<uint32_t>(p->launch.samples_per_thread);
     LaunchSpec spec{p->prec,  p->launch.block,    p->split ? 1 : 0, p->launch.persistent,
                     p->grid,  p->lat.observable, p->lat.antithetic};
-    if (p->launch.persistent)
+    // (a lent block's queue head came with its upload, and it runs once)
+    if (p->launch.persistent && p->d_block)
         BFI_HIP(launch_reset_head(p->d_head, st));
     if (timed)
         BFI_HIP(hipEventRecord(p->ev_start, st));
@@ -806,12 +930,12 @@ bfi_status plan_enqueue(bfi_plan *p, uint64_t seed, double *dst, hipStream_t st,
     m.sub_first = p->d_sub_first;
     m.sub_rec = p->d_sub_rec;
     m.sub_split = p->d_sub_split;
-    m.nsub = static_cast<uint32_t>(p->subs.size());
+    m.nsub = static_cast<uint32_t>(p->nsub);
     m.nx = p->nx;
     m.d = p->d;
     BFI_HIP(launch_merge(m, st));
     if (dst)
-        BFI_HIP(hipMemcpyAsync(dst, p->d_sub_rec, p->subs.size() * p->rec_len * sizeof(double),
+        BFI_HIP(hipMemcpyAsync(dst, p->d_sub_rec, p->nsub * p->rec_len * sizeof(double),
                                hipMemcpyDeviceToDevice, st));
     return BFI_OK;
 }
@@ -911,6 +1035,10 @@ bfi_status bfi_context_destroy(bfi_context *ctx)
             (void)hipStreamSynchronize(ctx->stream);
             (void)hipStreamDestroy(ctx->stream);
         }
+        if (ctx->scratch_dev)
+            (void)hipFree(ctx->scratch_dev);
+        if (ctx->scratch_host)
+            (void)hipHostFree(ctx->scratch_host);
         delete ctx;
         return BFI_OK;
     });
@@ -928,8 +1056,7 @@ bfi_status bfi_plan_create(bfi_context *ctx, const bfi_lattice *lat, bfi_precisi
         BFI_TRY(check_lattice(lat));
         BFI_TRY(check_subvolumes(lat, subs));
         BFI_HIP(hipSetDevice(ctx->device));
-        return plan_build(ctx, *lat, prec, SubList::copy_of(*subs, lat->nx * lat->nt), launch, false,
-                          out);
+        return plan_build(ctx, *lat, prec, *subs, launch, out);
     });
 }
 
@@ -1007,7 +1134,7 @@ bfi_status bfi_plan_partials(bfi_plan *p, double *partials)
         BFI_HIP(hipSetDevice(p->ctx->device));
         if (p->last_stream)
             BFI_HIP(hipStreamSynchronize(p->last_stream));
-        BFI_HIP(hipMemcpy(partials, p->d_sub_rec, p->subs.size() * p->rec_len * sizeof(double),
+        BFI_HIP(hipMemcpy(partials, p->d_sub_rec, p->nsub * p->rec_len * sizeof(double),
                           hipMemcpyDeviceToHost));
         return BFI_OK;
     });
@@ -1073,28 +1200,7 @@ bfi_status bfi_eval(bfi_context *ctx, const bfi_lattice *lat, bfi_precision prec
         if (subs->count == 0)
             return BFI_OK;
         BFI_HIP(hipSetDevice(ctx->device));
-        bfi_plan *p = nullptr;
-        {
-            TraceRange tb("bfi_eval: plan build and upload");
-            BFI_TRY(plan_build(ctx, *lat, prec, SubList::copy_of(*subs, lat->nx * lat->nt), launch,
-                               split != nullptr, &p));
-        }
-        bfi_launch l = p->launch;
-        l.use_graph = 0;
-        p->launch = l;
-        bfi_status s = plan_enqueue(p, seed, nullptr, ctx->stream, true);
-        p->last_stream = ctx->stream;
-        if (s == BFI_OK)
-            s = bfi_plan_partials(p, partials);
-        if (s == BFI_OK && split) {
-            hipError_t e = hipMemcpy(split, p->d_sub_split,
-                                     subs->count * BFI_SPLIT_LEN(p->d) * sizeof(double),
-                                     hipMemcpyDeviceToHost);
-            if (e != hipSuccess)
-                s = hip_fail(e, "hipMemcpy(split)");
-        }
-        plan_free(p);
-        return s;
+        return eval_once(ctx, *lat, prec, seed, *subs, launch, partials, split);
     });
 }
 

@@ -5,11 +5,13 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <array>
 #include <atomic>
 #include <cstdarg>
 #include <cstdint>
 #include <exception>
 #include <map>
+#include <mutex>
 #include <new>
 #include <string>
 #include <thread>
@@ -76,7 +78,6 @@ struct SubList {
     {
         return bfi_subvolumes{id.size(), id.data(), lo.data(), hi.data(), n.data(), offset.data()};
     }
-    static SubList copy_of(const bfi_subvolumes &s, int d);
 };
 
 // Uniform bisection of a box: 2^k leaves, level t halves dim t mod d at
@@ -292,6 +293,13 @@ struct bfi_context {
     hipStream_t stream = nullptr;
     std::string arch;
     std::map<bfi::TuneKey, bfi::TuneEntry> tuned;
+    // blocking calls' memory (CallScratch), one call at a time
+    std::mutex scratch_busy;
+    char *scratch_dev = nullptr, *scratch_host = nullptr;
+    size_t scratch_dev_cap = 0, scratch_host_cap = 0;
+    // blocks per CU of the kernel variants asked for so far
+    std::mutex occupancy_mutex;
+    std::map<std::array<int, 8>, int> occupancy;
 };
 
 // A resident evaluation: descriptors, work items and buffers on the device.
@@ -303,15 +311,14 @@ struct bfi_plan {
     int prec = 0;
     int d = 0, nx = 0, rec_len = 0;
     bool split = false;
-    bfi::SubList subs;
+    size_t nsub = 0;
     bfi_launch launch{};
     uint32_t nitems = 0;
     uint32_t grid = 0;
     uint64_t n_evals = 0;
 
-    double *d_base64 = nullptr, *d_scale64 = nullptr;
-    float *d_base32 = nullptr, *d_scale32 = nullptr;
-    uint64_t *d_ids = nullptr, *d_offsets = nullptr;
+    // the plan's own device memory (null where a call lends it), and its pieces
+    char *d_block = nullptr;
     bfi::EvalParams *d_params = nullptr;
     bfi::EvalParams params{};  // host copy of *d_params
     bfi::WorkItem *d_items = nullptr;
@@ -338,17 +345,63 @@ struct bfi_plan {
 };
 
 namespace bfi {
-bfi_status plan_build(bfi_context *ctx, const bfi_lattice &lat, int prec, const SubList &subs,
-                      const bfi_launch *launch, bool split, bfi_plan **out);
-// Plan for the Gaussian-proposal sampler: `streams` lists stream ids (bit 63:
-// uniform component), sample counts and offsets; lo/hi rows are the cube.
-bfi_status plan_build_is(bfi_context *ctx, const bfi_lattice &lat, int prec,
-                         const SubList &streams, const IsTable &table, const bfi_launch *launch,
-                         bfi_plan **out);
-// Plan for the N-sphere integrand over `dim`-dimensional boxes (FP64, split
-// statistics always on, 256-thread blocks); records have nx = 0.
-bfi_status plan_build_nsphere(bfi_context *ctx, int dim, const SubList &subs,
-                              const bfi_launch *launch, bfi_plan **out);
+// Device and pinned host memory of one blocking call on the context's stream:
+// the context's, kept from call to call, or -- while another call holds it, or
+// beyond kScratchLimit -- the call's own.  Given back by the destructor, which
+// first waits for the stream unless wait() has (an error path's copies may
+// still read the host block).
+//
+// A call used to allocate and free its 14 device buffers, copy nine arrays from
+// pageable memory and create two events: of 225 us for 2^16 evaluations of 4x2
+// the kernels were 21.  With one block and one copy each way it takes 44 us;
+// 2^26 evaluations of the Gaussian-proposal sampler over 512 streams 1.67 ->
+// 1.42 ms, 3.2e7 of the N-sphere integrand 544 -> 338 us.
+class CallScratch {
+public:
+    static constexpr size_t kScratchLimit = size_t(64) << 20;
+    CallScratch() = default;
+    ~CallScratch();
+    CallScratch(const CallScratch &) = delete;
+    CallScratch &operator=(const CallScratch &) = delete;
+    bfi_status take(bfi_context *ctx, size_t host_bytes, size_t dev_bytes);
+    char *host() const { return host_; }
+    char *dev() const { return dev_; }
+    // copy the first `bytes` of the host block to the device block
+    bfi_status upload(size_t bytes);
+    // copy `bytes` of the device block from `from` to the host block's start and
+    // wait for them
+    bfi_status download(size_t from, size_t bytes);
+
+private:
+    bfi_context *ctx_ = nullptr;
+    std::unique_lock<std::mutex> held_;
+    std::vector<char> own_host_;
+    char *own_dev_ = nullptr, *host_ = nullptr, *dev_ = nullptr;
+    bool queued_ = false;
+};
+
+// Blocks of one kernel variant that fill the chip once (kind as in bfi_plan; 3:
+// the sampler in spherical coordinates).
+bfi_status resident_blocks(bfi_context *ctx, int kind, const bfi_lattice &lat,
+                           const LaunchSpec &spec, uint64_t *blocks);
+
+bfi_status plan_build(bfi_context *ctx, const bfi_lattice &lat, int prec,
+                      const bfi_subvolumes &subs, const bfi_launch *launch, bfi_plan **out);
+// One blocking evaluation of a list on the context's stream: records to
+// `partials`, split statistics to `split` when non-NULL.
+//   eval_once: the lattice action over boxes.
+//   eval_once_nsphere: the N-sphere integrand over `dim`-dimensional boxes
+//     (FP64, split statistics always on, 256-thread blocks); records have nx = 0.
+//   eval_once_is: the Gaussian-proposal sampler; `streams` lists stream ids (bit
+//     63: uniform component), sample counts and offsets (lo, hi unused).
+bfi_status eval_once(bfi_context *ctx, const bfi_lattice &lat, int prec, uint64_t seed,
+                     const bfi_subvolumes &subs, const bfi_launch *launch, double *partials,
+                     double *split);
+bfi_status eval_once_nsphere(bfi_context *ctx, int dim, uint64_t seed, const bfi_subvolumes &subs,
+                             const bfi_launch *launch, double *partials, double *split);
+bfi_status eval_once_is(bfi_context *ctx, const bfi_lattice &lat, int prec, uint64_t seed,
+                        const bfi_subvolumes &streams, const IsTable &table,
+                        const bfi_launch *launch, double *partials);
 // timed: record the plan's events around the Monte Carlo kernel (not inside a
 // graph capture, where recorded events carry no timestamps)
 bfi_status plan_enqueue(bfi_plan *p, uint64_t seed, double *dst, hipStream_t stream, bool timed);

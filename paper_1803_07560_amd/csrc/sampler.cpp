@@ -110,21 +110,8 @@ IsTable make_table(const bfi_lattice &lat, double lo, double hi, double alpha, u
     return t;
 }
 
-SubList stream_list(int d, double lo, double hi, size_t count, const uint64_t *id,
-                    const uint64_t *n, const uint64_t *offset)
-{
-    SubList s;
-    s.d = d;
-    s.id.assign(id, id + count);
-    s.n.assign(n, n + count);
-    s.offset.assign(offset, offset + count);
-    s.lo.assign(count * d, lo);
-    s.hi.assign(count * d, hi);
-    return s;
-}
-
 bfi_status run_streams(bfi_context *ctx, const bfi_lattice &lat, int prec, uint64_t seed,
-                       double lo, double hi, double alpha, const SubList &streams,
+                       double lo, double hi, double alpha, const bfi_subvolumes &streams,
                        const bfi_launch *launch, double *partials, Modes *modes)
 {
     // the Philox counter index * blocks + j of the last sample must fit in 64
@@ -133,7 +120,7 @@ bfi_status run_streams(bfi_context *ctx, const bfi_lattice &lat, int prec, uint6
     const int d = lat.nx * lat.nt;
     const unsigned __int128 index_end = (static_cast<unsigned __int128>(1) << 64) /
                                         static_cast<unsigned>((2 * ((d + 1) / 2) + 1 + 3) / 4);
-    for (size_t s = 0; s < streams.size(); ++s) {
+    for (size_t s = 0; s < streams.count; ++s) {
         if (streams.n[s] < 2)
             return fail(BFI_EINVAL, "stream %zu has n = %llu < 2", s,
                         static_cast<unsigned long long>(streams.n[s]));
@@ -142,15 +129,7 @@ bfi_status run_streams(bfi_context *ctx, const bfi_lattice &lat, int prec, uint6
     }
     BFI_HIP(hipSetDevice(ctx->device));
     const IsTable table = make_table(lat, lo, hi, alpha, seed, modes);
-    bfi_plan *p = nullptr;
-    BFI_TRY(plan_build_is(ctx, lat, prec, streams, table, launch, &p));
-    p->launch.use_graph = 0;
-    bfi_status s = plan_enqueue(p, seed, nullptr, ctx->stream, true);
-    p->last_stream = ctx->stream;
-    if (s == BFI_OK)
-        s = bfi_plan_partials(p, partials);
-    plan_free(p);
-    return s;
+    return eval_once_is(ctx, lat, prec, seed, streams, table, launch, partials);
 }
 
 }  // namespace
@@ -191,8 +170,7 @@ bfi_status bfi_is_eval(bfi_context *ctx, const bfi_lattice *lat, bfi_precision p
         if (!stream_id || !n || !offset || !partials)
             return fail(BFI_EINVAL, "stream arrays and partials must be non-NULL");
         Modes m;
-        const SubList streams =
-            stream_list(lat->nx * lat->nt, box_lo, box_hi, count, stream_id, n, offset);
+        const bfi_subvolumes streams{count, stream_id, nullptr, nullptr, n, offset};
         return run_streams(ctx, *lat, prec, seed, box_lo, box_hi, gaussian_fraction, streams, launch,
                            partials, &m);
     });
@@ -229,8 +207,8 @@ bfi_status bfi_integrate_is(bfi_context *ctx, const bfi_lattice *lat, bfi_precis
             }
         }
         const int d = lat->nx * lat->nt, nx = lat->nx;
-        const SubList list = stream_list(d, box_lo, box_hi, ids.size(), ids.data(), ns.data(),
-                                         offs.data());
+        const bfi_subvolumes list{ids.size(), ids.data(), nullptr, nullptr, ns.data(),
+                                  offs.data()};
         std::vector<double> rec(ids.size() * BFI_PARTIAL_LEN(nx));
         Modes m;
         BFI_TRY(run_streams(ctx, *lat, prec, seed, box_lo, box_hi, gaussian_fraction, list, launch,

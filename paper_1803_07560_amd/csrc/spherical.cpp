@@ -106,33 +106,18 @@ bfi_status sph_eval(bfi_context *ctx, const bfi_lattice &lat, int prec, uint64_t
     if (l.samples_per_thread < 1 || l.samples_per_thread > (1 << 20))
         return fail(BFI_EINVAL, "samples_per_thread out of range");
     LaunchSpec spec{prec, l.block, 0, l.persistent, 0, lat.observable, 0};
-    KernelInfo info{};
-    BFI_HIP(sph_kernel_info(lat.nx, lat.nt, spec, &info));
-    const uint64_t resident = static_cast<uint64_t>(std::max(info.blocks_per_cu, 1)) *
-                              std::max(ctx->cu_count, 1);
+    uint64_t resident = 0;
+    BFI_TRY(resident_blocks(ctx, 3, lat, spec, &resident));
     const uint64_t chunk = item_samples(l, spread_items(prec, launch), sh.n, ns, resident);
-    std::vector<WorkItem> items;
-    std::vector<uint32_t> first(ns + 1);
+    uint64_t nitems = 0;
     for (size_t s = 0; s < ns; ++s) {
-        first[s] = static_cast<uint32_t>(items.size());
-        for (uint64_t start = 0; start < sh.n[s]; start += chunk) {
-            items.push_back(WorkItem{nullptr, nullptr, start, static_cast<uint32_t>(s),
-                                     static_cast<uint32_t>(std::min(chunk, sh.n[s] - start))});
-            if (items.size() > 0x7FFFFFFFull)
-                return fail(BFI_EINVAL, "more than 2^31 work items; raise samples_per_thread");
-        }
-    }
-    first[ns] = static_cast<uint32_t>(items.size());
-    std::vector<double> shell64(2 * ns);
-    std::vector<float> shell32(2 * ns);
-    for (size_t s = 0; s < ns; ++s) {
-        shell64[2 * s] = sh.rho_hi[s];
-        shell64[2 * s + 1] = inner_ratio(d, sh.rho_lo[s], sh.rho_hi[s]);
-        shell32[2 * s] = static_cast<float>(shell64[2 * s]);
-        shell32[2 * s + 1] = static_cast<float>(shell64[2 * s + 1]);
+        nitems += sh.n[s] / chunk + (sh.n[s] % chunk != 0);
+        if (nitems > 0x7FFFFFFFull)
+            return fail(BFI_EINVAL, "more than 2^31 work items; raise samples_per_thread");
     }
 
-    // one device block: parameters, ids, offsets, shells, items, records, head
+    // one device block: what the host writes first (parameters, ids, offsets,
+    // shells, items, queue head), then the records
     auto al = [](size_t x) { return (x + 255) & ~size_t(255); };
     size_t at = 0;
     auto take = [&](size_t bytes) {
@@ -140,45 +125,52 @@ bfi_status sph_eval(bfi_context *ctx, const bfi_lattice &lat, int prec, uint64_t
         at = al(at + bytes);
         return here;
     };
-    const size_t o_params = take(sizeof(EvalParams)), o_ids = take(ns * 8), o_off = take(ns * 8),
-                 o_s64 = take(ns * 16), o_s32 = take(ns * 8),
-                 o_items = take(items.size() * sizeof(WorkItem)), o_first = take((ns + 1) * 4),
-                 o_irec = take(items.size() * rec_len * 8), o_srec = take(ns * rec_len * 8),
-                 o_head = take(4);
-    DevMem mem;
-    BFI_HIP(hipMalloc(&mem.p, at));
-    char *base = static_cast<char *>(mem.p);
+    const size_t o_params = take(sizeof(EvalParams)), o_head = take(4), o_ids = take(ns * 8),
+                 o_off = take(ns * 8), o_s64 = take(ns * 16), o_s32 = take(ns * 8),
+                 o_first = take((ns + 1) * 4), o_items = take(nitems * sizeof(WorkItem)),
+                 image = at, o_srec = take(ns * rec_len * 8), o_irec = take(nitems * rec_len * 8);
+    const size_t rec_bytes = ns * rec_len * 8;
+    CallScratch scratch;
+    BFI_TRY(scratch.take(ctx, std::max(image, rec_bytes), at));
+    char *base = scratch.dev(), *img = scratch.host();
     auto *params = reinterpret_cast<EvalParams *>(base + o_params);
     const EvalParams P{nullptr, nullptr, nullptr, nullptr,
                        reinterpret_cast<const uint64_t *>(base + o_ids),
                        reinterpret_cast<const uint64_t *>(base + o_off), make_coef(lat),
                        static_cast<uint32_t>(seed), static_cast<uint32_t>(seed >> 32)};
-    for (size_t i = 0; i < items.size(); ++i) {
-        items[i].params = params;
-        items[i].rec = reinterpret_cast<double *>(base + o_irec) + i * rec_len;
+    std::memcpy(img + o_params, &P, sizeof(P));
+    std::memset(img + o_head, 0, 4);
+    std::memcpy(img + o_ids, sh.id, ns * 8);
+    std::memcpy(img + o_off, sh.offset, ns * 8);
+    auto *shell64 = reinterpret_cast<double *>(img + o_s64);
+    auto *shell32 = reinterpret_cast<float *>(img + o_s32);
+    auto *first = reinterpret_cast<uint32_t *>(img + o_first);
+    auto *items = reinterpret_cast<WorkItem *>(img + o_items);
+    uint32_t it = 0;
+    for (size_t s = 0; s < ns; ++s) {
+        shell64[2 * s] = sh.rho_hi[s];
+        shell64[2 * s + 1] = inner_ratio(d, sh.rho_lo[s], sh.rho_hi[s]);
+        shell32[2 * s] = static_cast<float>(shell64[2 * s]);
+        shell32[2 * s + 1] = static_cast<float>(shell64[2 * s + 1]);
+        first[s] = it;
+        for (uint64_t start = 0; start < sh.n[s]; start += chunk, ++it)
+            items[it] = WorkItem{params,
+                                 reinterpret_cast<double *>(base + o_irec) +
+                                     static_cast<size_t>(it) * rec_len,
+                                 start, static_cast<uint32_t>(s),
+                                 static_cast<uint32_t>(std::min(chunk, sh.n[s] - start))};
     }
+    first[ns] = it;
     hipStream_t st = ctx->stream;
-    BFI_HIP(hipMemcpyAsync(params, &P, sizeof(P), hipMemcpyHostToDevice, st));
-    BFI_HIP(hipMemcpyAsync(base + o_ids, sh.id, ns * 8, hipMemcpyHostToDevice, st));
-    BFI_HIP(hipMemcpyAsync(base + o_off, sh.offset, ns * 8, hipMemcpyHostToDevice, st));
-    BFI_HIP(hipMemcpyAsync(base + o_s64, shell64.data(), ns * 16, hipMemcpyHostToDevice, st));
-    BFI_HIP(hipMemcpyAsync(base + o_s32, shell32.data(), ns * 8, hipMemcpyHostToDevice, st));
-    BFI_HIP(hipMemcpyAsync(base + o_items, items.data(), items.size() * sizeof(WorkItem),
-                           hipMemcpyHostToDevice, st));
-    BFI_HIP(hipMemcpyAsync(base + o_first, first.data(), (ns + 1) * 4, hipMemcpyHostToDevice, st));
+    BFI_TRY(scratch.upload(image));
 
     auto *head = reinterpret_cast<uint32_t *>(base + o_head);
-    if (l.persistent) {
-        spec.grid = static_cast<uint32_t>(std::min<uint64_t>(resident, items.size()));
-        BFI_HIP(launch_reset_head(head, st));
-    } else {
-        spec.grid = static_cast<uint32_t>(items.size());
-    }
+    spec.grid = static_cast<uint32_t>(l.persistent ? std::min<uint64_t>(resident, nitems) : nitems);
     SphArgs a{};
     a.mc.items = reinterpret_cast<const WorkItem *>(base + o_items);
     a.mc.item_split = nullptr;
     a.mc.queue_head = l.persistent ? head : nullptr;
-    a.mc.nitems = static_cast<uint32_t>(items.size());
+    a.mc.nitems = static_cast<uint32_t>(nitems);
     a.mc.samples_per_thread = static_cast<uint32_t>(l.samples_per_thread);
     a.shell64 = reinterpret_cast<const double *>(base + o_s64);
     a.shell32 = reinterpret_cast<const float *>(base + o_s32);
@@ -193,8 +185,8 @@ bfi_status sph_eval(bfi_context *ctx, const bfi_lattice &lat, int prec, uint64_t
     m.nx = lat.nx;
     m.d = d;
     BFI_HIP(launch_merge(m, st));
-    BFI_HIP(hipMemcpyAsync(partials, base + o_srec, ns * rec_len * 8, hipMemcpyDeviceToHost, st));
-    BFI_HIP(hipStreamSynchronize(st));
+    BFI_TRY(scratch.download(o_srec, rec_bytes));
+    std::memcpy(partials, scratch.host(), rec_bytes);
     return BFI_OK;
 }
 

@@ -34,7 +34,7 @@ bfi_status time_candidate(bfi_context *ctx, const bfi_lattice &lat, int prec, co
                           const bfi_launch &cand, double *rate)
 {
     bfi_plan *p = nullptr;
-    BFI_TRY(plan_build(ctx, lat, prec, subs, &cand, false, &p));
+    BFI_TRY(plan_build(ctx, lat, prec, subs.view(), &cand, &p));
     Events ev;
     bfi_status s = BFI_OK;
     hipError_t e = hipEventCreate(&ev.a);

@@ -207,10 +207,13 @@ struct LeafAnalysisArgs {
 size_t analysis_scratch_doubles(uint32_t count, int nx);
 hipError_t launch_leaf_analysis(const LeafAnalysisArgs &args, hipStream_t stream);
 
+// N-sphere kernels (common_kernels.hip), one per dimension.
+hipError_t launch_nsphere(const NsphereArgs &args, uint32_t grid, hipStream_t stream);
+hipError_t nsphere_kernel_info(int dim, KernelInfo *info);
+
 // Shape-independent kernels (common_kernels.hip).
 hipError_t launch_build_items(const BuildArgs &args, hipStream_t stream);
 hipError_t launch_reset_head(uint32_t *head, hipStream_t stream);
-hipError_t launch_nsphere(const NsphereArgs &args, uint32_t grid, hipStream_t stream);
 hipError_t launch_merge(const MergeArgs &args, hipStream_t stream);
 hipError_t launch_debug_points(const DebugPointArgs &args, hipStream_t stream);
 

@@ -599,7 +599,7 @@ bfi_status resident_blocks(bfi_context *ctx, int kind, const bfi_lattice &lat,
         else if (kind == 3)
             e = sph_kernel_info(lat.nx, lat.nt, spec, &info);
         else
-            info.blocks_per_cu = 4;  // 104 VGPRs: 4 waves per SIMD, one block per SIMD
+            e = nsphere_kernel_info(lat.nx, &info);
         if (e != hipSuccess)
             return hip_fail(e, "kernel occupancy query");
         per_cu = std::max(info.blocks_per_cu, 1);
@@ -670,7 +670,10 @@ bfi_status plan_build_core(bfi_context *ctx, const PlanSpec &what, const bfi_sub
     if (static_cast<uint64_t>(l.samples_per_thread) * l.block > 0x7FFFFFFFull)
         return fail(BFI_EINVAL, "samples per work item exceed 2^31");
     uint64_t resident = 0;
-    BFI_TRY(resident_blocks(ctx, kind, lat,
+    bfi_lattice shape = lat;
+    if (kind == 1)
+        shape.nx = d;  // one kernel per dimension
+    BFI_TRY(resident_blocks(ctx, kind, shape,
                             LaunchSpec{prec, l.block, split ? 1 : 0, 1, 0, lat.observable,
                                        lat.antithetic},
                             &resident));

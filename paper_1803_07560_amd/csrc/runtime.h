@@ -380,8 +380,8 @@ private:
     bool queued_ = false;
 };
 
-// Blocks of one kernel variant that fill the chip once (kind as in bfi_plan; 3:
-// the sampler in spherical coordinates).
+// Blocks of one kernel variant that fill the chip once (kind as in bfi_plan, with
+// the N-sphere's dimension as nx; 3: the sampler in spherical coordinates).
 bfi_status resident_blocks(bfi_context *ctx, int kind, const bfi_lattice &lat,
                            const LaunchSpec &spec, uint64_t *blocks);
 

@@ -213,6 +213,36 @@ __device__ __forceinline__ void philox_block_item_at(uint32_t lo, uint64_t jA,
     philox_rounds_item(mad_wide(lo, kPhiloxMulA, jA), p, out);
 }
 
+// Blocks of one stream's samples for a kernel that takes them one at a time.
+// On items whose counters keep one upper word (same_hi), with the item's share
+// of Philox; else the whole block each time.
+struct PhiloxStream {
+    PhiloxItem item;
+    uint32_t id_lo, id_hi, key_lo, key_hi;
+    uint64_t first;  // counter of the item's first block
+    bool same_hi;
+
+    __device__ __forceinline__ PhiloxStream(uint64_t id, uint64_t first_index, uint32_t count,
+                                            int blocks, uint32_t seed_lo, uint32_t seed_hi)
+        : id_lo(static_cast<uint32_t>(id)), id_hi(static_cast<uint32_t>(id >> 32)),
+          key_lo(seed_lo), key_hi(seed_hi), first(first_index * static_cast<uint64_t>(blocks))
+    {
+        const uint64_t last = (first_index + count) * static_cast<uint64_t>(blocks) - 1;
+        same_hi = (first >> 32) == (last >> 32);
+        item = philox_item(static_cast<uint32_t>(first >> 32), id_lo, id_hi, key_lo, key_hi);
+    }
+    // the item's block `at` (0 .. count * blocks - 1, below 2^32: the samplers'
+    // items hold at most 2^20 x 256 samples of at most 9 blocks)
+    template <bool SAME_HI>
+    __device__ __forceinline__ void block(uint32_t at, uint32_t out[4]) const
+    {
+        if constexpr (SAME_HI)
+            philox_block_item(static_cast<uint32_t>(first) + at, item, out);
+        else
+            philox_block(first + at, id_lo, id_hi, key_lo, key_hi, out);
+    }
+};
+
 // Word -> coordinate: u = fma(x, scale, base), one rounding.
 __device__ __forceinline__ double map_word(uint32_t x, double scale, double base)
 {
@@ -380,8 +410,8 @@ __device__ __forceinline__ double row_move(double x)
 {
     const uint64_t b = __builtin_bit_cast(uint64_t, x);
     const int lo = static_cast<int>(b), hi = static_cast<int>(b >> 32);
-    const uint32_t l = __builtin_amdgcn_update_dpp(lo, lo, CTRL, 0xf, 0xf, false);
-    const uint32_t h = __builtin_amdgcn_update_dpp(hi, hi, CTRL, 0xf, 0xf, false);
+    const uint32_t l = __builtin_amdgcn_mov_dpp(lo, CTRL, 0xf, 0xf, true);
+    const uint32_t h = __builtin_amdgcn_mov_dpp(hi, CTRL, 0xf, 0xf, true);
     return __builtin_bit_cast(double, static_cast<uint64_t>(h) << 32 | l);
 }
 // Rotation within the row of 16 by R lanes.

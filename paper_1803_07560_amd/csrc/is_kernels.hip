@@ -187,12 +187,10 @@ struct Transform {
 
 // ------------------------------------------------------------- sampling
 
+template <class T>
+using TablesOf = std::conditional_t<std::is_same_v<T, double>, dev::NormalTables, dev::NoTables>;
+
 // log(exp(g1) + exp(g2)) with g2 possibly -inf
-__device__ __forceinline__ double log_add(double g1, double g2)
-{
-    const double mx = fmax(g1, g2), mn = fmin(g1, g2);
-    return mx + log1p(exp(mn - mx));
-}
 __device__ __forceinline__ float log_add(float g1, float g2)
 {
     constexpr float kLog2e = 1.44269504088896340736f, kLn2 = 0.69314718055994530942f;
@@ -200,27 +198,33 @@ __device__ __forceinline__ float log_add(float g1, float g2)
     return mx + kLn2 * __builtin_amdgcn_logf(1.0f + __builtin_amdgcn_exp2f((mn - mx) * kLog2e));
 }
 
+// Philox blocks of a sample: the normals' pairs of words, then one; or a word per
+// variable
+template <int D>
+constexpr int kGaussianBlocks = (2 * ((D + 1) / 2) + 1 + 3) / 4;
+template <int D>
+constexpr int kUniformBlocks = (D + 3) / 4;
+
 // One sample of the Gaussian component: coefficients from normals, the point
 // by the inverse transform; returns sum over Gaussian modes of z^2/2.
-template <class T, int NX, int NT>
-__device__ __forceinline__ T gaussian_point(uint64_t index, uint32_t id_lo, uint32_t id_hi,
-                                            uint32_t key_lo, uint32_t key_hi,
-                                            const T (&scale)[NX * NT], bool uniform0,
+template <class T, int NX, int NT, bool SAME_HI>
+__device__ __forceinline__ T gaussian_point(const dev::PhiloxStream &words, uint32_t local,
+                                            const TablesOf<T> &tab, const T (&scale)[NX * NT], bool uniform0,
                                             T (&u)[NX * NT])
 {
     constexpr int D = NX * NT;
     constexpr int kPairs = (D + 1) / 2;
-    constexpr int NB = (2 * kPairs + 1 + 3) / 4;  // words: the pairs, then one
+    constexpr int NB = kGaussianBlocks<D>;
     T a[D];
     T hz = T(0);
-    const uint64_t q0 = index * NB;
+    const uint32_t b0 = local * static_cast<uint32_t>(NB);
     uint32_t blk[4];
 #pragma unroll
     for (int p = 0; p < kPairs; ++p) {
         if ((p & 1) == 0)
-            dev::philox_block(q0 + (p >> 1), id_lo, id_hi, key_lo, key_hi, blk);
+            words.block<SAME_HI>(b0 + (p >> 1), blk);
         T zc, zs;
-        dev::box_muller(blk[2 * (p & 1)], blk[2 * (p & 1) + 1], zc, zs);
+        dev::box_muller(blk[2 * (p & 1)], blk[2 * (p & 1) + 1], tab, zc, zs);
         const int j0 = 2 * p, j1 = 2 * p + 1;
         a[j0] = scale[j0] * zc;
         const T h0 = T(0.5) * zc * zc;
@@ -235,7 +239,7 @@ __device__ __forceinline__ T gaussian_point(uint64_t index, uint32_t id_lo, uint
         // the constant mode: word 2 ceil(d/2), uniform over [-R, R]
         constexpr int w = 2 * kPairs;
         if constexpr ((w >> 2) != ((w - 1) >> 2))
-            dev::philox_block(q0 + (w >> 2), id_lo, id_hi, key_lo, key_hi, blk);
+            words.block<SAME_HI>(b0 + (w >> 2), blk);
         const double v = __fma_rn(static_cast<double>(blk[w & 3]), 0x1p-32, 0x1p-33);
         a[0] = static_cast<T>(static_cast<double>(scale[0]) * (2.0 * v - 1.0));
     }
@@ -245,20 +249,18 @@ __device__ __forceinline__ T gaussian_point(uint64_t index, uint32_t id_lo, uint
 
 // One sample of the uniform component: the plain sampler's words and point map
 // over the cube, then the Gaussian exponent of that point.
-template <class T, int NX, int NT>
-__device__ __forceinline__ T uniform_point(uint64_t index, uint32_t id_lo, uint32_t id_hi,
-                                           uint32_t key_lo, uint32_t key_hi, T map_base,
-                                           T map_scale, const T (&inv_scale)[NX * NT],
+template <class T, int NX, int NT, bool SAME_HI>
+__device__ __forceinline__ T uniform_point(const dev::PhiloxStream &words, uint32_t local,
+                                           T map_base, T map_scale, const T (&inv_scale)[NX * NT],
                                            bool uniform0, T (&u)[NX * NT])
 {
     constexpr int D = NX * NT;
-    constexpr int NB = (D + 3) / 4;
-    const uint64_t q0 = index * NB;
+    const uint32_t b0 = local * static_cast<uint32_t>(kUniformBlocks<D>);
     uint32_t blk[4];
 #pragma unroll
     for (int k = 0; k < D; ++k) {
         if ((k & 3) == 0)
-            dev::philox_block(q0 + (k >> 2), id_lo, id_hi, key_lo, key_hi, blk);
+            words.block<SAME_HI>(b0 + (k >> 2), blk);
         u[k] = dev::map_word(blk[k & 3], map_scale, map_base);
     }
     T a[D];
@@ -279,7 +281,9 @@ constexpr float kShiftGap = 64.0f;
 constexpr float kLog2e = 1.44269504088896340736f;
 
 template <int NX, int NT, int PREC, int BLOCK, bool AVG>
-__global__ void __launch_bounds__(BLOCK) is_kernel(IsArgs ia)
+__global__ void __launch_bounds__(BLOCK)
+    // three waves per SIMD in the FP32 form (4 registers over 168 otherwise)
+    __attribute__((amdgpu_waves_per_eu(PREC == kFP64 ? 1 : 3))) is_kernel(IsArgs ia)
 {
     using T = std::conditional_t<PREC == kFP64, double, float>;
     constexpr int D = NX * NT;
@@ -292,7 +296,11 @@ __global__ void __launch_bounds__(BLOCK) is_kernel(IsArgs ia)
     __shared__ double red[NW][NF];
     __shared__ float red_sigma[NW];
     __shared__ uint32_t next_item;
+    __shared__ TablesOf<T> tab64;
     const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = tid >> 6;
+    tab64.load(tid, BLOCK);
+    __syncthreads();
+    using ExpFma = dev::FmaSgprCoef;
 
     const IsTable *tab = ia.table;
     const T log_ga = static_cast<T>(dev::load_uniform(&tab->log_ga));
@@ -333,7 +341,6 @@ __global__ void __launch_bounds__(BLOCK) is_kernel(IsArgs ia)
         const uint32_t s = wi.sub;
         const uint64_t id = P.ids[s];
         const uint64_t first_index = P.offsets[s] + wi.start;
-        const uint32_t id_lo = static_cast<uint32_t>(id), id_hi = static_cast<uint32_t>(id >> 32);
 
         double acc[NF];
 #pragma unroll
@@ -347,8 +354,8 @@ __global__ void __launch_bounds__(BLOCK) is_kernel(IsArgs ia)
                 acc[i] *= (i == 0 || (i >= 2 && i < 2 + NR)) ? f1 : f2;
         };
 
-        // weight and sums of one point; hz = its sum z^2/2
-        auto accumulate = [&](const T (&u)[D], T hz, bool inside) {
+        // weight and sums of one point inside the cube; hz = its sum z^2/2
+        auto accumulate = [&](const T (&u)[D], T hz) {
             auto gen = [&](int l, T(&out)[NX], T) {
 #pragma unroll
                 for (int m = 0; m < NX; ++m)
@@ -356,8 +363,6 @@ __global__ void __launch_bounds__(BLOCK) is_kernel(IsArgs ia)
             };
             T first[NX];
             const T S = dev::action<T, NX, NT>(gen, first, coef, mass);
-            // -log of the weight W / K
-            const T L = S + log_add(log_ga - hz, log_un);
             T pr[NR];
             T pr_scale;
             if constexpr (AVG) {
@@ -381,7 +386,13 @@ __global__ void __launch_bounds__(BLOCK) is_kernel(IsArgs ia)
             }
             double w;
             if constexpr (PREC == kFP64) {
-                w = inside ? exp(-L) : 0.0;
+                // W / K = exp(-S) / (e^g1 + e^g2), the larger exponent taken out
+                // of the sum so that neither overflows
+                const double g1 = log_ga - hz, g2 = log_un;
+                const double mx = fmax(g1, g2), mn = fmin(g1, g2);
+                const double den = 1.0 + exp_weight<ExpFma>(mn - mx);
+                w = exp_weight<ExpFma>(-(S + mx)) *
+                    nrm::reciprocal(den, __builtin_amdgcn_rcp(den));
                 const double t = pr_scale * w;
 #pragma unroll
                 for (int r = 0; r < NR; ++r) {
@@ -391,11 +402,12 @@ __global__ void __launch_bounds__(BLOCK) is_kernel(IsArgs ia)
                     acc[2 + 2 * NR + r] = __fma_rn(v, w, acc[2 + 2 * NR + r]);
                 }
             } else {
-                if (inside && L < sigma - kShiftGap) {
+                const float L = S + log_add(log_ga - hz, log_un);  // -log(W / K)
+                if (L < sigma - kShiftGap) {
                     rescale(exp(static_cast<double>(L) - static_cast<double>(sigma)));
                     sigma = L;
                 }
-                const float w32 = inside ? __builtin_amdgcn_exp2f((sigma - L) * kLog2e) : 0.0f;
+                const float w32 = __builtin_amdgcn_exp2f((sigma - L) * kLog2e);
                 w = static_cast<double>(w32);
                 const float t32 = pr_scale * w32;
 #pragma unroll
@@ -417,40 +429,57 @@ __global__ void __launch_bounds__(BLOCK) is_kernel(IsArgs ia)
 #pragma unroll
             for (int j = 0; j < D; ++j)
                 inv_scale[j] = dev::load_uniform(inv_scale_g + j);
-            for (uint32_t k = 0; k < a.samples_per_thread; ++k) {
-                const uint32_t local = k * BLOCK + tid;
-                if (local >= wi.count)
-                    break;
-                T u[D];
-                const T hz = uniform_point<T, NX, NT>(first_index + local, id_lo, id_hi, P.seed_lo,
-                                                      P.seed_hi, map_base, map_scale, inv_scale,
-                                                      uniform0, u);
-                accumulate(u, hz, true);  // inside the cube by construction
-            }
+            const dev::PhiloxStream words(id, first_index, wi.count, kUniformBlocks<D>, P.seed_lo,
+                                          P.seed_hi);
+            auto samples = [&](auto same_hi_tag) {
+                for (uint32_t k = 0; k < a.samples_per_thread; ++k) {
+                    const uint32_t local = k * BLOCK + tid;
+                    if (local >= wi.count)
+                        break;
+                    T u[D];
+                    const T hz = uniform_point<T, NX, NT, decltype(same_hi_tag)::value>(
+                        words, local, map_base, map_scale, inv_scale, uniform0, u);
+                    accumulate(u, hz);  // inside the cube by construction
+                }
+            };
+            if (words.same_hi)
+                samples(std::true_type{});
+            else
+                samples(std::false_type{});
         } else {
             T scale[D];
 #pragma unroll
             for (int j = 0; j < D; ++j)
                 scale[j] = dev::load_uniform(scale_g + j);
-            for (uint32_t k = 0; k < a.samples_per_thread; ++k) {
-                const uint32_t local = k * BLOCK + tid;
-                if (local >= wi.count)
-                    break;
-                T u[D];
-                const T hz = gaussian_point<T, NX, NT>(first_index + local, id_lo, id_hi,
-                                                       P.seed_lo, P.seed_hi, scale, uniform0, u);
-                // inside the cube: its smallest and largest coordinates
-                // (three-operand min/max; a short-circuit test per coordinate
-                // compiles to a chain of divergent branches)
-                T umin = u[0], umax = u[0];
+            const dev::PhiloxStream words(id, first_index, wi.count, kGaussianBlocks<D>, P.seed_lo,
+                                          P.seed_hi);
+            auto samples = [&](auto same_hi_tag) {
+                for (uint32_t k = 0; k < a.samples_per_thread; ++k) {
+                    const uint32_t local = k * BLOCK + tid;
+                    if (local >= wi.count)
+                        break;
+                    T u[D];
+                    const T hz = gaussian_point<T, NX, NT, decltype(same_hi_tag)::value>(
+                        words, local, tab64, scale, uniform0, u);
+                    // inside the cube: its smallest and largest coordinates
+                    // (three-operand min/max; a short-circuit test per coordinate
+                    // compiles to a chain of divergent branches)
+                    T umin = u[0], umax = u[0];
 #pragma unroll
-                for (int j = 1; j < D; ++j) {
-                    umin = fmin(umin, u[j]);
-                    umax = fmax(umax, u[j]);
+                    for (int j = 1; j < D; ++j) {
+                        umin = fmin(umin, u[j]);
+                        umax = fmax(umax, u[j]);
+                    }
+                    // outside, the weight and every term of the sums are 0: a
+                    // wavefront wholly outside goes on to its next points
+                    if (lo <= umin && umax <= hi)
+                        accumulate(u, hz);
                 }
-                const bool inside = lo <= umin && umax <= hi;
-                accumulate(u, hz, inside);
-            }
+            };
+            if (words.same_hi)
+                samples(std::true_type{});
+            else
+                samples(std::false_type{});
         }
 
         // reduction: wavefront butterflies, then waves in order through LDS
@@ -516,6 +545,9 @@ __global__ void __launch_bounds__(256) is_debug_kernel(IsDebugArgs a)
 {
     using T = std::conditional_t<PREC == kFP64, double, float>;
     constexpr int D = NX * NT;
+    __shared__ TablesOf<T> tab64;
+    tab64.load(threadIdx.x, 256);
+    __syncthreads();
     const uint64_t i = static_cast<uint64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
     if (i >= a.n)
         return;
@@ -538,15 +570,16 @@ __global__ void __launch_bounds__(256) is_debug_kernel(IsDebugArgs a)
         map_base = tab->map_base32;
         map_scale = tab->map_scale32;
     }
-    const uint32_t id_lo = static_cast<uint32_t>(a.id), id_hi = static_cast<uint32_t>(a.id >> 32);
     T u[D];
     T hz;
     if (a.id & kIsUniformStream)
-        hz = uniform_point<T, NX, NT>(a.index[i], id_lo, id_hi, tab->seed_lo, tab->seed_hi,
-                                      map_base, map_scale, inv_scale, tab->uniform0 != 0, u);
+        hz = uniform_point<T, NX, NT, false>(
+            dev::PhiloxStream(a.id, a.index[i], 1, kUniformBlocks<D>, tab->seed_lo, tab->seed_hi), 0,
+            map_base, map_scale, inv_scale, tab->uniform0 != 0, u);
     else
-        hz = gaussian_point<T, NX, NT>(a.index[i], id_lo, id_hi, tab->seed_lo, tab->seed_hi,
-                                       scale, tab->uniform0 != 0, u);
+        hz = gaussian_point<T, NX, NT, false>(
+            dev::PhiloxStream(a.id, a.index[i], 1, kGaussianBlocks<D>, tab->seed_lo, tab->seed_hi),
+            0, tab64, scale, tab->uniform0 != 0, u);
     for (int k = 0; k < D; ++k)
         a.u_out[i * D + k] = static_cast<double>(u[k]);
     a.hz_out[i] = static_cast<double>(hz);

@@ -9,9 +9,9 @@
 // rho_hi)^d), and u = rho z / |z|: uniform in the shell's volume.  Inside the
 // cube the weight is exp(-S(u)) (Eq. Gen2), outside 0; the observables, FP64
 // sums, wavefront/LDS reduction and record layout are the plain kernel's, so
-// the finalize with shell volumes gives the integral.  FP64 form: library log,
-// sqrt, sincospi and pow; FP32 form: the hardware transcendentals and a shifted
-// weight, as in the plain kernel.
+// the finalize with shell volumes gives the integral.  FP64 form: logarithm,
+// sine, cosine and roots of normal64.hpp; FP32 form: the hardware transcendentals
+// and a shifted weight, as in the plain kernel.
 #include <type_traits>
 
 #include "device.hpp"
@@ -35,22 +35,24 @@ struct SphWords {
     static constexpr int kBlocks = (2 * kPairs + 1 + 3) / 4;
 };
 
-// The point of sample `index` of a shell.
-template <class T, int D>
-__device__ __forceinline__ void shell_point(uint64_t index, uint32_t id_lo, uint32_t id_hi,
-                                            uint32_t key_lo, uint32_t key_hi, T rho_hi, T t,
-                                            T (&u)[D])
+template <class T>
+using TablesOf = std::conditional_t<std::is_same_v<T, double>, dev::NormalTables, dev::NoTables>;
+
+// The point of the item's sample `local` of a shell.
+template <class T, int D, bool SAME_HI>
+__device__ __forceinline__ void shell_point(const dev::PhiloxStream &words, uint32_t local,
+                                            const TablesOf<T> &tab, T rho_hi, T t, T (&u)[D])
 {
     using W = SphWords<D>;
-    const uint64_t q0 = index * W::kBlocks;
+    const uint32_t b0 = local * static_cast<uint32_t>(W::kBlocks);
     uint32_t blk[4];
     T norm2 = T(0);
 #pragma unroll
     for (int p = 0; p < W::kPairs; ++p) {
         if ((p & 1) == 0)
-            dev::philox_block(q0 + (p >> 1), id_lo, id_hi, key_lo, key_hi, blk);
+            words.block<SAME_HI>(b0 + (p >> 1), blk);
         T zc, zs;
-        dev::box_muller(blk[2 * (p & 1)], blk[2 * (p & 1) + 1], zc, zs);
+        dev::box_muller(blk[2 * (p & 1)], blk[2 * (p & 1) + 1], tab, zc, zs);
         u[2 * p] = zc;
         norm2 = dev::fma_t(zc, zc, norm2);
         if (2 * p + 1 < D) {
@@ -60,13 +62,22 @@ __device__ __forceinline__ void shell_point(uint64_t index, uint32_t id_lo, uint
     }
     constexpr int w = W::kRadiusWord;
     if constexpr ((w >> 2) != ((w - 1) >> 2))
-        dev::philox_block(q0 + (w >> 2), id_lo, id_hi, key_lo, key_hi, blk);
+        words.block<SAME_HI>(b0 + (w >> 2), blk);
     const uint32_t xr = blk[w & 3];
     T f;
     if constexpr (std::is_same_v<T, double>) {
+        // rho = rho_hi y^(1/D), as exp(ln y / D) from D = 3 on (the logarithm's
+        // error is divided by D)
         const double v = __fma_rn(static_cast<double>(xr), 0x1p-32, 0x1p-33);
-        const double rho = rho_hi * pow(__fma_rn(v, 1.0 - t, t), 1.0 / D);
-        f = rho / sqrt(norm2);
+        const double y = __fma_rn(v, 1.0 - t, t);
+        double rho;
+        if constexpr (D == 1)
+            rho = rho_hi * y;
+        else if constexpr (D == 2)
+            rho = rho_hi * nrm::root(y, __builtin_amdgcn_rsq(y));
+        else
+            rho = rho_hi * exp_weight<dev::FmaSgprCoef>(nrm::minus_2log<0>(y, tab.log) * (-0.5 / D));
+        f = rho * nrm::reciprocal_root(norm2, __builtin_amdgcn_rsq(norm2));
     } else {
         const float v = __fmaf_rn(static_cast<float>(xr), 0x1p-32f, 0x1p-33f);
         const float y = __fmaf_rn(v, 1.0f - t, t);
@@ -93,7 +104,10 @@ __global__ void __launch_bounds__(BLOCK) sph_kernel(SphArgs sa)
     __shared__ double red[NW][NF];
     __shared__ float red_sigma[NW];
     __shared__ uint32_t next_item;
+    __shared__ TablesOf<T> tab;
     const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = tid >> 6;
+    tab.load(tid, BLOCK);
+    __syncthreads();
     const T box = PREC == kFP64 ? static_cast<T>(sa.box64) : static_cast<T>(sa.box32);
     const T inv_sites = T(1) / T(D);
     using ExpFma = std::conditional_t<PREC == kFP32Shifted, dev::FmaSgprCoef, dev::FmaVgprCoef>;
@@ -114,9 +128,8 @@ __global__ void __launch_bounds__(BLOCK) sph_kernel(SphArgs sa)
         const dev::Coef<T> coef(P.coef);
         const bool mass = P.coef.half_m2 != 0.0;
         const uint32_t s = wi.sub;
-        const uint64_t id = P.ids[s];
-        const uint64_t first_index = P.offsets[s] + wi.start;
-        const uint32_t id_lo = static_cast<uint32_t>(id), id_hi = static_cast<uint32_t>(id >> 32);
+        const dev::PhiloxStream words(P.ids[s], P.offsets[s] + wi.start, wi.count,
+                                      SphWords<D>::kBlocks, P.seed_lo, P.seed_hi);
         T rho_hi, t;
         if constexpr (PREC == kFP64) {
             rho_hi = dev::load_uniform(sa.shell64 + 2 * static_cast<size_t>(s));
@@ -138,13 +151,14 @@ __global__ void __launch_bounds__(BLOCK) sph_kernel(SphArgs sa)
                 acc[i] *= (i == 0 || (i >= 2 && i < 2 + NR)) ? f1 : f2;
         };
 
+        auto samples = [&](auto same_hi_tag) {
+        constexpr bool kSameHi = decltype(same_hi_tag)::value;
         for (uint32_t k = 0; k < a.samples_per_thread; ++k) {
             const uint32_t local = k * BLOCK + tid;
             if (local >= wi.count)
                 break;
             T u[D];
-            shell_point<T, D>(first_index + local, id_lo, id_hi, P.seed_lo, P.seed_hi, rho_hi, t,
-                              u);
+            shell_point<T, D, kSameHi>(words, local, tab, rho_hi, t, u);
             // inside the cube: the largest |u_j| (three-operand max; a
             // short-circuit test per coordinate compiles to a chain of
             // divergent branches)
@@ -152,7 +166,10 @@ __global__ void __launch_bounds__(BLOCK) sph_kernel(SphArgs sa)
 #pragma unroll
             for (int j = 1; j < D; ++j)
                 umax = fmax(umax, fabs(u[j]));
-            const bool inside = umax <= box;
+            // outside, the weight and every term of the sums are 0: a wavefront
+            // wholly outside (the outer shells) goes on to its next points
+            if (!(umax <= box))
+                continue;
             auto gen = [&](int l, T(&out)[NX], T) {
 #pragma unroll
                 for (int m = 0; m < NX; ++m)
@@ -183,7 +200,7 @@ __global__ void __launch_bounds__(BLOCK) sph_kernel(SphArgs sa)
             }
             double w;
             if constexpr (PREC == kFP64) {
-                w = inside ? exp_weight<ExpFma>(-S, efma) : 0.0;
+                w = exp_weight<ExpFma>(-S, efma);
                 const double tw = pr_scale * w;
 #pragma unroll
                 for (int r = 0; r < NR; ++r) {
@@ -193,11 +210,11 @@ __global__ void __launch_bounds__(BLOCK) sph_kernel(SphArgs sa)
                     acc[2 + 2 * NR + r] = __fma_rn(v, w, acc[2 + 2 * NR + r]);
                 }
             } else {
-                if (inside && S < sigma - kShiftGap) {
+                if (S < sigma - kShiftGap) {
                     rescale(exp(static_cast<double>(S) - static_cast<double>(sigma)));
                     sigma = S;
                 }
-                const float w32 = inside ? __builtin_amdgcn_exp2f((sigma - S) * kLog2e) : 0.0f;
+                const float w32 = __builtin_amdgcn_exp2f((sigma - S) * kLog2e);
                 w = static_cast<double>(w32);
                 const float t32 = pr_scale * w32;
 #pragma unroll
@@ -211,6 +228,11 @@ __global__ void __launch_bounds__(BLOCK) sph_kernel(SphArgs sa)
             acc[0] += w;
             acc[1] = __fma_rn(w, w, acc[1]);
         }
+        };
+        if (words.same_hi)
+            samples(std::true_type{});
+        else
+            samples(std::false_type{});
 
         // reduction: wavefront butterflies, then waves in order through LDS
         float wave_sigma = 0.0f;
@@ -277,12 +299,15 @@ template <int D, int PREC>
 __global__ void __launch_bounds__(256) sph_debug_kernel(SphDebugArgs a)
 {
     using T = std::conditional_t<PREC == kFP64, double, float>;
+    __shared__ TablesOf<T> tab;
+    tab.load(threadIdx.x, 256);
+    __syncthreads();
     const uint64_t i = static_cast<uint64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
     if (i >= a.n)
         return;
     T u[D];
-    shell_point<T, D>(a.index[i], static_cast<uint32_t>(a.id), static_cast<uint32_t>(a.id >> 32),
-                      a.seed_lo, a.seed_hi, static_cast<T>(a.rho_hi), static_cast<T>(a.t), u);
+    const dev::PhiloxStream words(a.id, a.index[i], 1, SphWords<D>::kBlocks, a.seed_lo, a.seed_hi);
+    shell_point<T, D, false>(words, 0, tab, static_cast<T>(a.rho_hi), static_cast<T>(a.t), u);
 #pragma unroll
     for (int k = 0; k < D; ++k)
         a.out[i * D + k] = static_cast<double>(u[k]);

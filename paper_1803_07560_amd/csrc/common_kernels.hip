@@ -3,6 +3,7 @@
 // point-emitting test hook.
 #include <type_traits>
 
+#include "bfi.h"
 #include "device.hpp"
 
 namespace bfi {
@@ -73,41 +74,70 @@ __global__ void reset_head_kernel(uint32_t *head)
         *head = 0u;
 }
 
-// One block per subvolume; thread f merges field f over the subvolume's items
-// in item order with Neumaier compensation, after moving every item to the
-// smallest shift of the subvolume (factor exp(sigma_min - sigma_item) for
-// first-order sums, its square for second-order sums; 1 in FP64 form).  Items
-// are read kMergeBatch at a time, all loads of a batch issued before its
-// arithmetic (the sums keep item order), so that a subvolume of many items
-// is not one load latency per item.
+// One block per subvolume: its items in GROUPS consecutive runs, a wavefront
+// each; thread f of a wavefront merges field f over its run in item order with
+// Neumaier compensation, after moving every item to the smallest shift of the
+// subvolume (factor exp(sigma_min - sigma_item) for first-order sums, its square
+// for second-order sums; 1 in FP64 form); the runs' sums and compensations then
+// merge in order.  Items are read kMergeBatch at a time, all loads of a batch
+// issued before its arithmetic (the sums keep item order).  What bounds it is
+// latency: a wavefront takes about a microsecond per batch, so the work items
+// per subvolume decide how many share them (launch_merge).  Measured, one
+// wavefront -> by that rule, whole calls: N-sphere
+// integrand, 3.2e7 samples in 32 subvolumes of 122 items 201 -> 174 us; spherical
+// sampler, 2^24 over 64 shells of up to some thousand items 695 -> 640 us.
 constexpr uint32_t kMergeBatch = 8;
+constexpr int kMergeMaxFields = BFI_PARTIAL_LEN(BFI_MAX_NX) + 2 * 32;
 
-__global__ void __launch_bounds__(64) merge_kernel(MergeArgs m)
+struct Compensated {
+    double sum = 0.0, comp = 0.0;
+    __device__ __forceinline__ void add(double v)
+    {
+        const double t = sum + v;
+        comp += fabs(sum) >= fabs(v) ? (sum - t) + v : (v - t) + sum;
+        sum = t;
+    }
+};
+
+template <int GROUPS>
+__global__ void __launch_bounds__(64 * GROUPS) merge_kernel(MergeArgs m)
 {
+    __shared__ double part[GROUPS > 1 ? GROUPS : 1][GROUPS > 1 ? kMergeMaxFields : 1][2];
+    __shared__ double low[GROUPS];
     const uint32_t s = blockIdx.x;
-    if (s >= m.nsub)
-        return;
+    const uint32_t lane = threadIdx.x & 63u, group = threadIdx.x >> 6;
     const int nx = m.nx, d = m.d;
     const int rec_len = 4 + 3 * nx;
-    const int split_len = m.item_split ? 2 * d : 0;
+    const int fields = rec_len + (m.item_split ? 2 * d : 0);
     const uint32_t i0 = m.sub_first[s], i1 = m.sub_first[s + 1];
 
+    // the smallest shift: items over the threads
     double sigma = __builtin_inf();
-    for (uint32_t i = i0; i < i1; i += kMergeBatch) {
-        double sg[kMergeBatch];
+    for (uint32_t i = i0 + threadIdx.x; i < i1; i += 64 * GROUPS)
+        sigma = fmin(sigma, m.item_rec[static_cast<size_t>(i) * rec_len + 1]);
+    sigma = dev::wave_min(sigma);
+    if constexpr (GROUPS > 1) {
+        if (lane == 0)
+            low[group] = sigma;
+        __syncthreads();
 #pragma unroll
-        for (uint32_t j = 0; j < kMergeBatch; ++j)
-            sg[j] = i + j < i1 ? m.item_rec[static_cast<size_t>(i + j) * rec_len + 1]
-                               : __builtin_inf();
-#pragma unroll
-        for (uint32_t j = 0; j < kMergeBatch; ++j)
-            sigma = fmin(sigma, sg[j]);
+        for (int g = 0; g < GROUPS; ++g)
+            sigma = fmin(sigma, low[g]);
     }
     if (i0 == i1)
         sigma = 0.0;
 
+    const uint32_t per = (i1 - i0 + GROUPS - 1) / GROUPS;
+    const uint32_t a = i0 + group * per < i1 ? i0 + group * per : i1;
+    const uint32_t b = a + per < i1 ? a + per : i1;
     double *out = m.sub_rec + static_cast<size_t>(s) * rec_len;
-    for (int f = threadIdx.x; f < rec_len + split_len; f += blockDim.x) {
+    auto store = [&](int f, const Compensated &c) {
+        if (f < rec_len)
+            out[f] = c.sum + c.comp;
+        else
+            m.sub_split[static_cast<size_t>(s) * (1 + 2 * d) + 1 + (f - rec_len)] = c.sum + c.comp;
+    };
+    for (int f = static_cast<int>(lane); f < fields; f += 64) {
         if (f == 1)
             continue;
         int order;
@@ -115,12 +145,12 @@ __global__ void __launch_bounds__(64) merge_kernel(MergeArgs m)
             order = f == 0 ? 0 : f == 2 ? 1 : f == 3 ? 2 : f < 4 + nx ? 1 : 2;
         else
             order = (f - rec_len) < d ? 1 : 2;
-        double sum = 0.0, comp = 0.0;
-        for (uint32_t i = i0; i < i1; i += kMergeBatch) {
+        Compensated c;
+        for (uint32_t i = a; i < b; i += kMergeBatch) {
             double vb[kMergeBatch], sb[kMergeBatch];
 #pragma unroll
             for (uint32_t j = 0; j < kMergeBatch; ++j) {
-                if (i + j < i1) {
+                if (i + j < b) {
                     const double *rec = m.item_rec + static_cast<size_t>(i + j) * rec_len;
                     vb[j] = f < rec_len ? rec[f]
                                         : m.item_split[static_cast<size_t>(i + j) * (2 * d) +
@@ -130,22 +160,36 @@ __global__ void __launch_bounds__(64) merge_kernel(MergeArgs m)
             }
 #pragma unroll
             for (uint32_t j = 0; j < kMergeBatch; ++j) {
-                if (i + j < i1) {
+                if (i + j < b) {
                     double v = vb[j];
                     if (order != 0) {
                         const double f1 = exp(sigma - sb[j]);
                         v *= order == 1 ? f1 : f1 * f1;
                     }
-                    const double t = sum + v;
-                    comp += fabs(sum) >= fabs(v) ? (sum - t) + v : (v - t) + sum;
-                    sum = t;
+                    c.add(v);
                 }
             }
         }
-        if (f < rec_len)
-            out[f] = sum + comp;
-        else
-            m.sub_split[static_cast<size_t>(s) * (1 + 2 * d) + 1 + (f - rec_len)] = sum + comp;
+        if constexpr (GROUPS > 1) {
+            part[group][f][0] = c.sum;
+            part[group][f][1] = c.comp;
+        } else {
+            store(f, c);
+        }
+    }
+    if constexpr (GROUPS > 1) {
+        __syncthreads();
+        for (int f = static_cast<int>(threadIdx.x); f < fields; f += 64 * GROUPS) {
+            if (f == 1)
+                continue;
+            Compensated c;
+#pragma unroll
+            for (int g = 0; g < GROUPS; ++g) {
+                c.add(part[g][f][0]);
+                c.add(part[g][f][1]);
+            }
+            store(f, c);
+        }
     }
     if (threadIdx.x == 0) {
         out[1] = sigma;
@@ -387,7 +431,22 @@ hipError_t launch_merge(const MergeArgs &args, hipStream_t stream)
 {
     if (args.nsub == 0)
         return hipSuccess;
-    hipLaunchKernelGGL(merge_kernel, dim3(args.nsub), dim3(64), 0, stream, args);
+    if (4 + 3 * args.nx + (args.item_split ? 2 * args.d : 0) > kMergeMaxFields)
+        return hipErrorInvalidValue;
+    // wavefronts per subvolume: one for up to two batches of items, four for up to
+    // eight, else sixteen.  The largest subvolume decides while the blocks fit the
+    // chip together (2048 of up to 16 wavefronts are four rounds); of longer lists
+    // the average does, whose few large subvolumes end beside the others.
+    const uint64_t items = args.nsub <= 2048
+                               ? args.most
+                               : static_cast<uint64_t>(args.nitems) / args.nsub;
+    const uint64_t batches = (items + kMergeBatch - 1) / kMergeBatch;
+    if (batches <= 2)
+        hipLaunchKernelGGL(merge_kernel<1>, dim3(args.nsub), dim3(64), 0, stream, args);
+    else if (batches <= 8)
+        hipLaunchKernelGGL(merge_kernel<4>, dim3(args.nsub), dim3(256), 0, stream, args);
+    else
+        hipLaunchKernelGGL(merge_kernel<16>, dim3(args.nsub), dim3(1024), 0, stream, args);
     return hipGetLastError();
 }
 

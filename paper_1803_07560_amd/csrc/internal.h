@@ -84,6 +84,7 @@ struct MergeArgs {
     double *sub_rec;            // nsub x rec_len
     double *sub_split;          // nsub x (1 + 2d) or null
     uint32_t nsub;
+    uint32_t nitems, most;      // items of the whole list, and of its largest subvolume
     int32_t nx, d;
 };
 

@@ -143,13 +143,15 @@ extern "C" bfi_status bfi_eval_noalloc(bfi_context *ctx, const bfi_lattice *lat,
         const size_t nsub = subs->count;
         const int rec_len = BFI_PARTIAL_LEN(lat->nx);
         bool spread = spread_items(prec, launch);
-        uint64_t chunk = 0, nitems = 0;
+        uint64_t chunk = 0, nitems = 0, most = 0;
         Layout L{};
         for (;;) {
             chunk = item_samples(l, spread, subs->n, nsub, resident);
-            nitems = 0;
+            nitems = most = 0;
             for (size_t s = 0; s < nsub; ++s) {
-                nitems += subs->n[s] / chunk + (subs->n[s] % chunk != 0);
+                const uint64_t count = subs->n[s] / chunk + (subs->n[s] % chunk != 0);
+                nitems += count;
+                most = std::max(most, count);
                 if (nitems > 0x7FFFFFFFull)
                     return fail(BFI_EINVAL, "more than 2^31 work items; raise samples_per_thread");
             }
@@ -220,6 +222,8 @@ extern "C" bfi_status bfi_eval_noalloc(bfi_context *ctx, const bfi_lattice *lat,
         m.sub_rec = sub_rec;
         m.sub_split = sub_split;
         m.nsub = static_cast<uint32_t>(nsub);
+        m.nitems = static_cast<uint32_t>(nitems);
+        m.most = static_cast<uint32_t>(most);
         m.nx = lat->nx;
         m.d = d;
         BFI_HIP(launch_merge(m, st));

@@ -680,12 +680,14 @@ bfi_status plan_build_core(bfi_context *ctx, const PlanSpec &what, const bfi_sub
 
     // work items: ceil(n / chunk) per subvolume, subvolumes in list order
     const uint64_t chunk = item_samples(l, spread_items(prec, launch), subs.n, nsub, resident);
-    uint64_t nitems = 0, n_evals = 0;
+    uint64_t nitems = 0, most = 0, n_evals = 0;
     for (size_t s = 0; s < nsub; ++s) {
         // checked per subvolume, so the running count cannot wrap
-        nitems += subs.n[s] / chunk + (subs.n[s] % chunk != 0);
+        const uint64_t count = subs.n[s] / chunk + (subs.n[s] % chunk != 0);
+        nitems += count;
         if (nitems > 0x7FFFFFFFull)
             return fail(BFI_EINVAL, "more than 2^31 work items; raise samples_per_thread");
+        most = std::max(most, count);
         n_evals += subs.n[s];
     }
     if (lat.antithetic)
@@ -748,6 +750,7 @@ bfi_status plan_build_core(bfi_context *ctx, const PlanSpec &what, const bfi_sub
     p->nsub = nsub;
     p->launch = l;
     p->nitems = static_cast<uint32_t>(nitems);
+    p->most_items = static_cast<uint32_t>(most);
     p->n_evals = n_evals;
     p->d_params = reinterpret_cast<EvalParams *>(dev + o_params);
     p->d_head = reinterpret_cast<uint32_t *>(dev + o_head);
@@ -934,6 +937,8 @@ bfi_status plan_enqueue(bfi_plan *p, uint64_t seed, double *dst, hipStream_t st,
     m.sub_rec = p->d_sub_rec;
     m.sub_split = p->d_sub_split;
     m.nsub = static_cast<uint32_t>(p->nsub);
+    m.nitems = p->nitems;
+    m.most = p->most_items;
     m.nx = p->nx;
     m.d = p->d;
     BFI_HIP(launch_merge(m, st));

@@ -313,7 +313,7 @@ struct bfi_plan {
     bool split = false;
     size_t nsub = 0;
     bfi_launch launch{};
-    uint32_t nitems = 0;
+    uint32_t nitems = 0, most_items = 0;  // of the list, and of its largest subvolume
     uint32_t grid = 0;
     uint64_t n_evals = 0;
 

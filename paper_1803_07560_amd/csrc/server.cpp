@@ -351,6 +351,9 @@ void complete(bfi_server *srv)
         m.sub_first = r->d_sub_first;
         m.sub_rec = r->d_sub_rec;
         m.nsub = static_cast<uint32_t>(r->subs.size());
+        m.nitems = static_cast<uint32_t>(r->items.size());
+        for (size_t k = 0; k < r->subs.size(); ++k)
+            m.most = std::max(m.most, r->sub_first[k + 1] - r->sub_first[k]);
         m.nx = r->nx;
         m.d = r->d;
         host[i] = reinterpret_cast<double *>(srv->h_done + at);

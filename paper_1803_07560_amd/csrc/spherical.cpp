@@ -109,9 +109,11 @@ bfi_status sph_eval(bfi_context *ctx, const bfi_lattice &lat, int prec, uint64_t
     uint64_t resident = 0;
     BFI_TRY(resident_blocks(ctx, 3, lat, spec, &resident));
     const uint64_t chunk = item_samples(l, spread_items(prec, launch), sh.n, ns, resident);
-    uint64_t nitems = 0;
+    uint64_t nitems = 0, most = 0;
     for (size_t s = 0; s < ns; ++s) {
-        nitems += sh.n[s] / chunk + (sh.n[s] % chunk != 0);
+        const uint64_t count = sh.n[s] / chunk + (sh.n[s] % chunk != 0);
+        nitems += count;
+        most = std::max(most, count);
         if (nitems > 0x7FFFFFFFull)
             return fail(BFI_EINVAL, "more than 2^31 work items; raise samples_per_thread");
     }
@@ -182,6 +184,8 @@ bfi_status sph_eval(bfi_context *ctx, const bfi_lattice &lat, int prec, uint64_t
     m.sub_first = reinterpret_cast<const uint32_t *>(base + o_first);
     m.sub_rec = reinterpret_cast<double *>(base + o_srec);
     m.nsub = static_cast<uint32_t>(ns);
+    m.nitems = static_cast<uint32_t>(nitems);
+    m.most = static_cast<uint32_t>(most);
     m.nx = lat.nx;
     m.d = d;
     BFI_HIP(launch_merge(m, st));

@@ -322,7 +322,8 @@ __global__ void __launch_bounds__(256) nsphere_kernel(McArgs a)
             if (tid < 2)
                 wi.rec[2 + tid] = total;
             else
-                a.item_split[static_cast<size_t>(it) * (2 * DIM) + (tid - 2)] = total;
+                a.item_split[static_cast<size_t>(wi.rec - a.item_rec) / BFI_PARTIAL_LEN(0) * (2 * DIM) +
+                             (tid - 2)] = total;
         }
         if (tid == 0) {
             wi.rec[0] = static_cast<double>(wi.count);

@@ -50,7 +50,9 @@ struct WorkItem {
 };
 
 struct McArgs {
-    const WorkItem *items;   // nitems
+    const WorkItem *items;   // nitems, in the order in which they are taken
+    const double *item_rec;  // with split statistics: the record of the list's first
+                             // item; an item's split row is that of its record
     double *item_split;      // nitems x 2d (split statistics), or null
     uint32_t *queue_head;    // persistent kernels: next item to take
     uint32_t nitems;

@@ -209,6 +209,7 @@ extern "C" bfi_status bfi_eval_noalloc(bfi_context *ctx, const bfi_lattice *lat,
         }
         McArgs a{};
         a.items = items;
+        a.item_rec = item_rec;
         a.item_split = item_split;
         a.queue_head = l.persistent ? head : nullptr;
         a.nitems = static_cast<uint32_t>(nitems);

@@ -329,6 +329,7 @@ bfi_status ResidentEval::enqueue(size_t nsub, uint64_t nitems, hipStream_t st)
                     lat_.observable, lat_.antithetic};
     McArgs a{};
     a.items = d_items_;
+    a.item_rec = d_item_rec_;
     a.item_split = split_ ? d_item_split_ : nullptr;
     a.queue_head = d_head_;
     a.nitems = static_cast<uint32_t>(nitems);

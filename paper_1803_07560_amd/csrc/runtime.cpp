@@ -334,6 +334,29 @@ uint64_t item_samples(const bfi_launch &l, bool spread, const uint64_t *n, size_
     return best;
 }
 
+void list_items(uint64_t chunk, const uint64_t *n, size_t nsub, const EvalParams *params,
+                double *item_rec, int rec_len, uint32_t *first, WorkItem *items)
+{
+    uint64_t whole = 0;
+    for (size_t s = 0; s < nsub; ++s)
+        whole += n[s] / chunk;
+    WorkItem *w = items, *const rests = items + whole, *r = rests;
+    uint32_t slot = 0;
+    for (size_t s = 0; s < nsub; ++s) {
+        first[s] = slot;
+        for (uint64_t start = 0; start < n[s]; start += chunk, ++slot) {
+            const uint64_t count = std::min(chunk, n[s] - start);
+            *(count == chunk ? w : r)++ =
+                WorkItem{params, item_rec + static_cast<size_t>(slot) * rec_len, start,
+                         static_cast<uint32_t>(s), static_cast<uint32_t>(count)};
+        }
+    }
+    first[nsub] = slot;
+    const auto longer = [](const WorkItem &a, const WorkItem &b) { return a.count > b.count; };
+    if (!std::is_sorted(rests, r, longer))
+        std::stable_sort(rests, r, longer);
+}
+
 namespace {
 
 // Neumaier-compensated sum.
@@ -798,16 +821,8 @@ bfi_status plan_build_core(bfi_context *ctx, const PlanSpec &what, const bfi_sub
     std::memcpy(img + o_ids, subs.id, nsub * 8);
     std::memcpy(img + o_offsets, subs.offset, nsub * 8);
     auto *first = reinterpret_cast<uint32_t *>(img + o_first);
-    auto *items = reinterpret_cast<WorkItem *>(img + o_items);
-    uint32_t it = 0;
-    for (size_t s = 0; s < nsub; ++s) {
-        first[s] = it;
-        for (uint64_t start = 0; start < subs.n[s]; start += chunk, ++it)
-            items[it] = WorkItem{p->d_params, p->d_item_rec + static_cast<size_t>(it) * rec_len,
-                                 start, static_cast<uint32_t>(s),
-                                 static_cast<uint32_t>(std::min<uint64_t>(chunk, subs.n[s] - start))};
-    }
-    first[nsub] = it;
+    list_items(chunk, subs.n, nsub, p->d_params, p->d_item_rec, rec_len, first,
+               reinterpret_cast<WorkItem *>(img + o_items));
     if (scratch) {
         BFI_TRY(scratch->upload(image));
     } else {
@@ -911,6 +926,7 @@ bfi_status plan_enqueue(bfi_plan *p, uint64_t seed, double *dst, hipStream_t st,
     BFI_TRY(plan_set_seed(p, seed));
     McArgs a{};
     a.items = p->d_items;
+    a.item_rec = p->d_item_rec;
     a.item_split = p->d_item_split;
     a.queue_head = p->launch.persistent ? p->d_head : nullptr;
     a.nitems = p->nitems;

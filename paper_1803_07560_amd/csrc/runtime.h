@@ -165,6 +165,16 @@ inline bool spread_items(int prec, const bfi_launch *req)
 uint64_t item_samples(const bfi_launch &l, bool spread, const uint64_t *n, size_t nsub,
                       uint64_t resident);
 
+// Work items of a list: record slots in list order (sub_first: first slot of each
+// subvolume, nsub + 1 entries), the items themselves in the order in which blocks
+// shall take them, whole ones first and then the subvolumes' rests by falling
+// length, so that the last round ends on the shortest.  (The records do not
+// depend on the order.)  Measured, list order -> this, whole calls: 2^26
+// evaluations of the Gaussian-proposal sampler over 512 streams 1.38 -> 1.33 ms,
+// 301 uneven leaves with split statistics 257 -> 250 us.
+void list_items(uint64_t chunk, const uint64_t *n, size_t nsub, const EvalParams *params,
+                double *item_rec, int rec_len, uint32_t *sub_first, WorkItem *items);
+
 // Host finalize of partial records (see bfi_finalize).
 // evals_per_sample: integrand evaluations behind one record sample (2 for
 // antithetic pairs), for n_evals.  leaf_var (nsub doubles, or NULL) gets each

@@ -622,7 +622,8 @@ __global__ void __launch_bounds__(BLOCK)
             if (i < F::kRecord)
                 rec[2 + i] = total;
             else
-                a.item_split[static_cast<size_t>(it) * (2 * D) + (i - F::kRecord)] = total;
+                a.item_split[static_cast<size_t>(rec - a.item_rec) / (2 + F::kRecord) * (2 * D) +
+                             (i - F::kRecord)] = total;
         }
         if (tid == 0) {
             rec[0] = static_cast<double>(wi.count);

@@ -146,23 +146,15 @@ bfi_status sph_eval(bfi_context *ctx, const bfi_lattice &lat, int prec, uint64_t
     std::memcpy(img + o_off, sh.offset, ns * 8);
     auto *shell64 = reinterpret_cast<double *>(img + o_s64);
     auto *shell32 = reinterpret_cast<float *>(img + o_s32);
-    auto *first = reinterpret_cast<uint32_t *>(img + o_first);
-    auto *items = reinterpret_cast<WorkItem *>(img + o_items);
-    uint32_t it = 0;
     for (size_t s = 0; s < ns; ++s) {
         shell64[2 * s] = sh.rho_hi[s];
         shell64[2 * s + 1] = inner_ratio(d, sh.rho_lo[s], sh.rho_hi[s]);
         shell32[2 * s] = static_cast<float>(shell64[2 * s]);
         shell32[2 * s + 1] = static_cast<float>(shell64[2 * s + 1]);
-        first[s] = it;
-        for (uint64_t start = 0; start < sh.n[s]; start += chunk, ++it)
-            items[it] = WorkItem{params,
-                                 reinterpret_cast<double *>(base + o_irec) +
-                                     static_cast<size_t>(it) * rec_len,
-                                 start, static_cast<uint32_t>(s),
-                                 static_cast<uint32_t>(std::min(chunk, sh.n[s] - start))};
     }
-    first[ns] = it;
+    list_items(chunk, sh.n, ns, params, reinterpret_cast<double *>(base + o_irec), rec_len,
+               reinterpret_cast<uint32_t *>(img + o_first),
+               reinterpret_cast<WorkItem *>(img + o_items));
     hipStream_t st = ctx->stream;
     BFI_TRY(scratch.upload(image));
 

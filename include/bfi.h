@@ -570,8 +570,10 @@ typedef struct {
     int32_t chunks_per_step;    /* work items per request per step, at least */
     int32_t max_pending;        /* submitted but not admitted; EBUSY beyond it */
     uint64_t step_evals;        /* target evaluations per step, shared equally by the
-                                   active requests (0: 2^25); bounds the wait of a
-                                   newly admitted request for the running step */
+                                   active requests, what short ones leave of their
+                                   share going to the others (0: 2^25); bounds the
+                                   wait of a newly admitted request for the running
+                                   step */
     int32_t max_samples_per_thread; /* cap on the tuned samples per thread of served
                                    work items (0: 128).  An item is the unit of a
                                    request's progress: small items spread a small

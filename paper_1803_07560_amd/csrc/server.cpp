@@ -7,8 +7,8 @@
 // parameters and one partial record per item) is allocated when it is
 // admitted, which happens in arrival order while the memory budget and the
 // request slots allow.  A worker thread runs scheduling steps: every admitted
-// request contributes an equal share of the step's evaluation target (at least
-// `chunks_per_step` items) from its remaining items, the step's items are
+// request contributes a share of the step's evaluation target (step_share; at
+// least `chunks_per_step` items) from its remaining items, the step's items are
 // grouped by (shape, precision) and each group is drained by one persistent
 // kernel through a device queue, the groups on separate streams so kernels of
 // different shapes overlap on the chip; requests that finish are merged on
@@ -466,6 +466,25 @@ bfi_status run_step(bfi_server *srv, const std::vector<StepEntry> &entries)
     return BFI_OK;
 }
 
+// A request's share of a step of `total` evaluations over requests with `left`
+// evaluations to go: what shorter requests leave of an equal share goes to the
+// longer ones, so a step below its target cuts nobody.  With equal shares
+// whatever was left, a burst of 16 requests (2^16 .. 2^22 evaluations, 2^24 in
+// all, target 2^25) ran its longest four over two steps, each as long as the
+// slowest item: 1.43 -> 1.18 .. 1.28 ms for the burst.
+uint64_t step_share(std::vector<uint64_t> left, uint64_t total)
+{
+    std::sort(left.begin(), left.end());
+    uint64_t share = total;
+    for (size_t i = 0; i < left.size(); ++i) {
+        share = total / (left.size() - i);
+        if (left[i] >= share)
+            return share;
+        total -= left[i];
+    }
+    return std::max(share, left.empty() ? share : left.back());
+}
+
 void worker_loop(bfi_server *srv)
 {
     (void)hipSetDevice(srv->ctx->device);
@@ -477,21 +496,26 @@ void worker_loop(bfi_server *srv)
         std::vector<StepEntry> entries;
         const size_t na = srv->admitted.size();
         size_t budget = srv->step_cap;
-        size_t active = 0;
+        // evaluations that each active request has left, in whole items
+        auto item_evals = [](const Request *r) {
+            // (an item of antithetic pairs makes two evaluations per sample index)
+            return static_cast<uint64_t>(r->launch.samples_per_thread) * r->launch.block *
+                   (r->req.lat.antithetic ? 2 : 1);
+        };
+        std::vector<uint64_t> left;
         for (uint64_t t : srv->admitted) {
             const Request *r = srv->reqs.at(t).get();
-            active += !r->cancel && r->next_item < r->items.size();
+            if (!r->cancel && r->next_item < r->items.size())
+                left.push_back((r->items.size() - r->next_item) * item_evals(r));
         }
-        const uint64_t step_evals = srv->cfg.step_evals ? srv->cfg.step_evals : uint64_t(1) << 25;
+        const uint64_t share = step_share(
+            std::move(left), srv->cfg.step_evals ? srv->cfg.step_evals : uint64_t(1) << 25);
         for (size_t k = 0; k < na && budget > 0; ++k) {
             Request *r = srv->reqs.at(srv->admitted[(srv->rr + k) % na]).get();
             if (r->cancel || r->next_item >= r->items.size())
                 continue;
-            // equal share of the step's evaluations, at least chunks_per_step items
-            // (an item of antithetic pairs makes two evaluations per sample index)
-            const uint64_t chunk = static_cast<uint64_t>(r->launch.samples_per_thread) *
-                                   r->launch.block * (r->req.lat.antithetic ? 2 : 1);
-            const uint64_t share = step_evals / std::max<size_t>(active, 1);
+            // a share of the step's evaluations, at least chunks_per_step items
+            const uint64_t chunk = item_evals(r);
             const size_t quota = std::max<size_t>(static_cast<size_t>(srv->cfg.chunks_per_step),
                                                   static_cast<size_t>((share + chunk - 1) / chunk));
             const size_t take = std::min({quota, r->items.size() - r->next_item, budget});

@@ -87,6 +87,7 @@ __global__ void reset_head_kernel(uint32_t *head)
 // integrand, 3.2e7 samples in 32 subvolumes of 122 items 201 -> 174 us; spherical
 // sampler, 2^24 over 64 shells of up to some thousand items 695 -> 640 us.
 constexpr uint32_t kMergeBatch = 8;
+// (one wavefront for long runs: MergeArgs with nitems and most 0)
 constexpr int kMergeMaxFields = BFI_PARTIAL_LEN(BFI_MAX_NX) + 2 * 32;
 
 struct Compensated {

@@ -54,8 +54,8 @@ bfi_status eval_records(bfi_context *ctx, const bfi_integrand &f, int d, uint64_
     split->assign(subs.count * BFI_SPLIT_LEN(d), 0.0);
     if (f.kind == BFI_INTEGRAND_NSPHERE)
         return eval_once_nsphere(ctx, d, seed, subs, launch, rec->data(), split->data());
-    return bfi_eval(ctx, &f.lat, static_cast<bfi_precision>(f.prec), seed, &subs, launch,
-                    rec->data(), split->data());
+    BFI_TRY(check_subvolumes(&f.lat, &subs));
+    return eval_once(ctx, f.lat, f.prec, seed, subs, launch, rec->data(), split->data(), true);
 }
 
 struct Estimate {

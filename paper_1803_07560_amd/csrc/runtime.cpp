@@ -645,6 +645,7 @@ struct PlanSpec {
     uint64_t seed;
     const bfi_launch *launch;
     const IsTable *table;  // kind 2
+    bool fixed_order = false;  // sums in the launch shape's order (see eval_once)
 };
 
 bfi_status plan_build_core(bfi_context *ctx, const PlanSpec &what, const bfi_subvolumes &subs,
@@ -702,7 +703,8 @@ bfi_status plan_build_core(bfi_context *ctx, const PlanSpec &what, const bfi_sub
                             &resident));
 
     // work items: ceil(n / chunk) per subvolume, subvolumes in list order
-    const uint64_t chunk = item_samples(l, spread_items(prec, launch), subs.n, nsub, resident);
+    const uint64_t chunk = item_samples(l, spread_items(prec, launch) && !what.fixed_order, subs.n,
+                                        nsub, resident);
     uint64_t nitems = 0, most = 0, n_evals = 0;
     for (size_t s = 0; s < nsub; ++s) {
         // checked per subvolume, so the running count cannot wrap
@@ -774,6 +776,7 @@ bfi_status plan_build_core(bfi_context *ctx, const PlanSpec &what, const bfi_sub
     p->launch = l;
     p->nitems = static_cast<uint32_t>(nitems);
     p->most_items = static_cast<uint32_t>(most);
+    p->fixed_order = what.fixed_order;
     p->n_evals = n_evals;
     p->d_params = reinterpret_cast<EvalParams *>(dev + o_params);
     p->d_head = reinterpret_cast<uint32_t *>(dev + o_head);
@@ -875,11 +878,11 @@ bfi_status plan_build(bfi_context *ctx, const bfi_lattice &lat, int prec,
 
 bfi_status eval_once(bfi_context *ctx, const bfi_lattice &lat, int prec, uint64_t seed,
                      const bfi_subvolumes &subs, const bfi_launch *launch, double *partials,
-                     double *split)
+                     double *split, bool fixed_order)
 {
     return run_once(ctx,
                     PlanSpec{0, lat, lat.nx * lat.nt, lat.nx, prec, split != nullptr, seed, launch,
-                             nullptr},
+                             nullptr, fixed_order},
                     subs, partials, split);
 }
 
@@ -891,7 +894,7 @@ bfi_status eval_once_nsphere(bfi_context *ctx, int dim, uint64_t seed, const bfi
     bfi_lattice none{};
     none.nx = 0;
     none.nt = 1;
-    return run_once(ctx, PlanSpec{1, none, dim, 0, kFP64, true, seed, launch, nullptr}, subs,
+    return run_once(ctx, PlanSpec{1, none, dim, 0, kFP64, true, seed, launch, nullptr, true}, subs,
                     partials, split);
 }
 
@@ -953,8 +956,10 @@ bfi_status plan_enqueue(bfi_plan *p, uint64_t seed, double *dst, hipStream_t st,
     m.sub_rec = p->d_sub_rec;
     m.sub_split = p->d_sub_split;
     m.nsub = static_cast<uint32_t>(p->nsub);
-    m.nitems = p->nitems;
-    m.most = p->most_items;
+    if (!p->fixed_order) {
+        m.nitems = p->nitems;
+        m.most = p->most_items;
+    }
     m.nx = p->nx;
     m.d = p->d;
     BFI_HIP(launch_merge(m, st));

@@ -324,6 +324,7 @@ struct bfi_plan {
     size_t nsub = 0;
     bfi_launch launch{};
     uint32_t nitems = 0, most_items = 0;  // of the list, and of its largest subvolume
+    bool fixed_order = false;  // one-wavefront merge: sums in the launch shape's order
     uint32_t grid = 0;
     uint64_t n_evals = 0;
 
@@ -399,14 +400,19 @@ bfi_status plan_build(bfi_context *ctx, const bfi_lattice &lat, int prec,
                       const bfi_subvolumes &subs, const bfi_launch *launch, bfi_plan **out);
 // One blocking evaluation of a list on the context's stream: records to
 // `partials`, split statistics to `split` when non-NULL.
-//   eval_once: the lattice action over boxes.
+//   eval_once: the lattice action over boxes.  fixed_order: items of the launch
+//     shape and a merge by one wavefront, for callers that decide by the split
+//     statistics.  Where a few samples carry a subvolume's weight, two
+//     dimensions' spreads are equal but for the last bits of the sums, and
+//     another order of summation would suggest another dimension.
 //   eval_once_nsphere: the N-sphere integrand over `dim`-dimensional boxes
-//     (FP64, split statistics always on, 256-thread blocks); records have nx = 0.
+//     (FP64, split statistics always on, 256-thread blocks, fixed order);
+//     records have nx = 0.
 //   eval_once_is: the Gaussian-proposal sampler; `streams` lists stream ids (bit
 //     63: uniform component), sample counts and offsets (lo, hi unused).
 bfi_status eval_once(bfi_context *ctx, const bfi_lattice &lat, int prec, uint64_t seed,
                      const bfi_subvolumes &subs, const bfi_launch *launch, double *partials,
-                     double *split);
+                     double *split, bool fixed_order = false);
 bfi_status eval_once_nsphere(bfi_context *ctx, int dim, uint64_t seed, const bfi_subvolumes &subs,
                              const bfi_launch *launch, double *partials, double *split);
 bfi_status eval_once_is(bfi_context *ctx, const bfi_lattice &lat, int prec, uint64_t seed,

@@ -82,11 +82,12 @@ __global__ void reset_head_kernel(uint32_t *head)
 // merge in order.  Items are read kMergeBatch at a time, all loads of a batch
 // issued before its arithmetic (the sums keep item order).  What bounds it is
 // latency: a wavefront takes about a microsecond per batch, so the work items
-// per subvolume decide how many share them (launch_merge).  Measured, one
-// wavefront -> by that rule, whole calls: N-sphere
-// integrand, 3.2e7 samples in 32 subvolumes of 122 items 201 -> 174 us; spherical
-// sampler, 2^24 over 64 shells of up to some thousand items 695 -> 640 us.
-constexpr uint32_t kMergeBatch = 8;
+// per subvolume decide how many share them (launch_merge).  Measured, whole
+// calls: spherical sampler, 2^24 over 64 shells of up to some thousand items,
+// one wavefront and batches of 8 695 us, by the rule 623 us, batches of 16 601
+// us; 301 uneven leaves with split statistics 250 -> 237 us by the longer
+// batches.
+constexpr uint32_t kMergeBatch = 16;
 // (one wavefront for long runs: MergeArgs with nitems and most 0)
 constexpr int kMergeMaxFields = BFI_PARTIAL_LEN(BFI_MAX_NX) + 2 * 32;
 
@@ -163,8 +164,9 @@ __global__ void __launch_bounds__(64 * GROUPS) merge_kernel(MergeArgs m)
             for (uint32_t j = 0; j < kMergeBatch; ++j) {
                 if (i + j < b) {
                     double v = vb[j];
-                    if (order != 0) {
-                        const double f1 = exp(sigma - sb[j]);
+                    const double by = sigma - sb[j];
+                    if (order != 0 && by != 0.0) {  // (a factor of 1 left out)
+                        const double f1 = exp(by);
                         v *= order == 1 ? f1 : f1 * f1;
                     }
                     c.add(v);
@@ -435,17 +437,17 @@ hipError_t launch_merge(const MergeArgs &args, hipStream_t stream)
         return hipSuccess;
     if (4 + 3 * args.nx + (args.item_split ? 2 * args.d : 0) > kMergeMaxFields)
         return hipErrorInvalidValue;
-    // wavefronts per subvolume: one for up to two batches of items, four for up to
-    // eight, else sixteen.  The largest subvolume decides while the blocks fit the
+    // wavefronts per subvolume: one for one batch of items, four for up to four,
+    // else sixteen.  The largest subvolume decides while the blocks fit the
     // chip together (2048 of up to 16 wavefronts are four rounds); of longer lists
     // the average does, whose few large subvolumes end beside the others.
     const uint64_t items = args.nsub <= 2048
                                ? args.most
                                : static_cast<uint64_t>(args.nitems) / args.nsub;
     const uint64_t batches = (items + kMergeBatch - 1) / kMergeBatch;
-    if (batches <= 2)
+    if (batches <= 1)
         hipLaunchKernelGGL(merge_kernel<1>, dim3(args.nsub), dim3(64), 0, stream, args);
-    else if (batches <= 8)
+    else if (batches <= 4)
         hipLaunchKernelGGL(merge_kernel<4>, dim3(args.nsub), dim3(256), 0, stream, args);
     else
         hipLaunchKernelGGL(merge_kernel<16>, dim3(args.nsub), dim3(1024), 0, stream, args);

@@ -1,7 +1,7 @@
 """The merge of work-item records with one, four and sixteen wavefronts per
 subvolume: against numpy's merge of the items' own records, which come from the
 same samples listed as one subvolume per item.  Items per subvolume around the
-edges of a batch (8 items), of the rule (16, 64) and of the runs' lengths, empty
+edges of a batch (16 items), of the rule (16, 64) and of the runs' lengths, empty
 runs among them (65 items are 13 runs of 5 for 16 wavefronts).  The sums are
 compensated on both sides, so they agree to a few roundings; 1e-13 of each
 sum's L1 scale."""

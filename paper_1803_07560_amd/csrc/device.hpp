@@ -393,16 +393,6 @@ __device__ __forceinline__ T load_uniform(const T *p)
     return out;
 }
 
-// Butterfly sum across the 64 lanes of a wavefront; every lane ends with the
-// same bits (each step adds the same two operands in both partner lanes).
-__device__ __forceinline__ double wave_sum(double v)
-{
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1)
-        v += __shfl_xor(v, off, 64);
-    return v;
-}
-
 // x of the lane `CTRL` selects within the row of 16 (a data-parallel move: one
 // vector instruction per dword, no trip through LDS).
 template <int CTRL>
@@ -437,6 +427,19 @@ __device__ __forceinline__ double halve(double a, double b)
                               : __builtin_amdgcn_permlane16_swap(xh, yh, false, false);
     return __builtin_bit_cast(double, static_cast<uint64_t>(hi[0]) << 32 | lo[0]) +
            __builtin_bit_cast(double, static_cast<uint64_t>(hi[1]) << 32 | lo[1]);
+}
+
+// Butterfly sum across the 64 lanes of a wavefront (lane distances 32, 16, 8, 4, 2,
+// 1); every lane ends with the same bits (each step adds the same two operands
+// in both partner lanes).
+__device__ __forceinline__ double wave_sum(double v)
+{
+    v = halve<2>(v, v);
+    v = halve<1>(v, v);
+    v += row_rotate<8>(v);
+    v += row_rotate<4>(v);
+    v += row_rotate<2>(v);
+    return v + row_rotate<1>(v);
 }
 
 // Sums of N fields over the wavefront, field i = value(i), into out[i] (LDS).

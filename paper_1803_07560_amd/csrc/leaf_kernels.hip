@@ -4,8 +4,8 @@
 // their delta-method errors, and the refinement's split choice, section 3).
 // The arithmetic is the host's (finalize_records, merge_shifted, split_choice)
 // operation for operation, without contraction into fused multiply-adds; only
-// the order of the sums over leaves differs (tree sums per block, blocks in
-// order with Neumaier compensation).
+// the order of the sums over leaves differs (tree sums per wavefront, groups of
+// wavefronts in order with Neumaier compensation).
 #include "device.hpp"
 
 #pragma clang fp contract(off)
@@ -25,113 +25,113 @@ __device__ __forceinline__ int split_class(int f, int d)
     return f == 0 ? 1 : f <= d ? 2 : 3;
 }
 
-// a <- a merged with b (disjoint samples of one leaf), both moved to the
-// smaller shift; counts add where there is a count.
-__device__ void merge_into(double *a, const double *b, int len, bool is_split, int nx, int d)
+// Field value a merged with b (disjoint samples of one leaf, shifts sa and sb),
+// both moved to the smaller shift; counts add, a shift becomes the smaller one.
+__device__ __forceinline__ double merge_field(double a, double b, double sa, double sb, int cls)
 {
-    const int sa = is_split ? 0 : 1;
-    const double sig = b[sa] < a[sa] ? b[sa] : a[sa];
-    const double fa = exp(sig - a[sa]), fb = exp(sig - b[sa]);
-    for (int f = 0; f < len; ++f) {
-        const int c = is_split ? split_class(f, d) : rec_class(f, nx);
-        if (c == 2)
-            a[f] = fa * a[f] + fb * b[f];
-        else if (c == 3)
-            a[f] = fa * fa * a[f] + fb * fb * b[f];
-        else if (c == 0)
-            a[f] += b[f];
-    }
-    a[sa] = sig;
+    const double sig = sb < sa ? sb : sa;
+    if (cls == 1)
+        return sig;
+    if (cls == 0)
+        return a + b;
+    const double fa = exp(sig - sa), fb = exp(sig - sb);
+    return cls == 2 ? fa * a + fb * b : fa * fa * a + fb * fb * b;
 }
 
-// The record of an entry's samples from its two parts (either may be absent),
-// written to out: the first part, then the second merged in (a part with no
-// samples adds nothing).
-__device__ void combine_parts(double *out, const double *w, const double *p, int rec_len, int nx,
-                              int d)
-{
-    if (w)
-        for (int f = 0; f < rec_len; ++f)
-            out[f] = w[f];
-    else
-        for (int f = 0; f < rec_len; ++f)
-            out[f] = 0.0;
-    if (!p || p[0] == 0)
-        return;
-    if (out[0] == 0) {
-        for (int f = 0; f < rec_len; ++f)
-            out[f] = p[f];
-        return;
-    }
-    merge_into(out, p, rec_len, false, nx, d);
-}
+// One wavefront per entry, a lane per field (every entry has a leaf of its own),
+// so that an entry's records are read and written in whole lines; with a thread
+// per entry the rows of 34 to 41 doubles went through 64 lines at a time and a
+// record in scratch memory.  What bounds it is latency.  Measured, 512 to 1024
+// entries of 10x2: 26 us with a thread per entry, 4.3 us with a wavefront.
+constexpr int kFoldBlock = 256;
 
-constexpr int kFoldBlock = 128;
-constexpr int kMaxRecLen = 4 + 3 * kMaxAnalysisNx;
-
-// One thread per entry; every entry has a leaf of its own.
 __global__ void __launch_bounds__(kFoldBlock) fold_kernel(FoldArgs a)
 {
-    const uint32_t i = blockIdx.x * kFoldBlock + threadIdx.x;
+    const uint32_t i = (blockIdx.x * kFoldBlock + threadIdx.x) >> 6;
+    const int lane = static_cast<int>(threadIdx.x & 63u);
     if (i >= a.count)
         return;
     const FoldEntry en = a.entries[i];
     const int nx = a.nx, d = a.d, rec_len = 4 + 3 * nx, split_len = 1 + 2 * d;
-    const double *w = en.wpos >= 0 ? a.with_rec + static_cast<size_t>(en.wpos) * rec_len : nullptr;
-    const double *sp =
-        en.wpos >= 0 ? a.with_split + static_cast<size_t>(en.wpos) * split_len : nullptr;
-    const double *p = en.opos >= 0 ? a.plain_rec + static_cast<size_t>(en.opos) * rec_len : nullptr;
+    const bool has_w = en.wpos >= 0, has_p = en.opos >= 0;
+    const double *w = a.with_rec + static_cast<size_t>(has_w ? en.wpos : 0) * rec_len;
+    const double *sp = a.with_split + static_cast<size_t>(has_w ? en.wpos : 0) * split_len;
+    const double *p = a.plain_rec + static_cast<size_t>(has_p ? en.opos : 0) * rec_len;
     double *lrec = a.leaf_rec + static_cast<size_t>(en.dst) * rec_len;
     double *lsplit = a.leaf_split + static_cast<size_t>(en.dst) * split_len;
     double *lbase = a.leaf_base + static_cast<size_t>(en.dst) * rec_len;
+    // counts and shifts first: the stores below replace the leaf's
+    const double wn = has_w ? w[0] : 0.0, ws = has_w ? w[1] : 0.0;
+    const double pn = has_p ? p[0] : 0.0, ps = has_p ? p[1] : 0.0;
+    // the record of the entry's samples from its two parts (either may be absent):
+    // the first part, then the second merged in (a part with no samples adds
+    // nothing)
+    const bool only_w = !has_p || pn == 0, only_p = !only_w && wn == 0;
+    auto part = [&](int f) -> double {
+        const double x = has_w ? w[f] : 0.0;
+        if (only_w)
+            return x;
+        return only_p ? p[f] : merge_field(x, p[f], ws, ps, rec_class(f, nx));
+    };
     if (en.kind == 0) {
-        double R[kMaxRecLen];
-        combine_parts(R, w, p, rec_len, nx, d);
-        merge_into(lrec, R, rec_len, false, nx, d);
-        if (w && w[0] > 0) {
+        const double rs = only_w ? ws : only_p ? ps : ps < ws ? ps : ws;
+        const double ls = lrec[1], ss = lsplit[0], bs = lbase[1], sps = has_w ? sp[0] : 0.0;
+        for (int f = lane; f < rec_len; f += 64)
+            lrec[f] = merge_field(lrec[f], part(f), ls, rs, rec_class(f, nx));
+        if (has_w && wn > 0) {
             // the continuation still lies below the split statistics' cut
-            merge_into(lsplit, sp, split_len, true, nx, d);
-            merge_into(lbase, w, rec_len, false, nx, d);
+            for (int f = lane; f < split_len; f += 64)
+                lsplit[f] = merge_field(lsplit[f], sp[f], ss, sps, split_class(f, d));
+            for (int f = lane; f < rec_len; f += 64)
+                lbase[f] = merge_field(lbase[f], w[f], bs, ws, rec_class(f, nx));
         }
         return;
     }
-    combine_parts(lrec, w, p, rec_len, nx, d);
-    for (int f = 0; f < split_len; ++f)
-        lsplit[f] = sp ? sp[f] : 0.0;
-    for (int f = 0; f < rec_len; ++f)
-        lbase[f] = w ? w[f] : 0.0;
-    a.leaf_vol[en.dst] = en.vol;
+    for (int f = lane; f < rec_len; f += 64) {
+        lrec[f] = part(f);
+        lbase[f] = has_w ? w[f] : 0.0;
+    }
+    for (int f = lane; f < split_len; f += 64)
+        lsplit[f] = has_w ? sp[f] : 0.0;
+    if (lane == 0)
+        a.leaf_vol[en.dst] = en.vol;
 }
 
 // ---- analysis ----------------------------------------------------------------
 
-// scratch layout (doubles): per block the smallest shift, the first pass's
-// 4 + nx sums and the second pass's nx sums; then [sigma, z, 1/z^2, C(r)]
-__device__ __forceinline__ size_t nblocks_of(uint32_t count)
+// Leaves are summed in fixed groups whatever the launch: 64 leaves by a
+// wavefront's butterfly, 16 of those sums in order (a group of kAnalysisBlock
+// leaves), the groups in order with Neumaier compensation.  A block holds four
+// wavefronts, so that a few thousand leaves use more than a few CUs; what bounds
+// each of these kernels at such sizes is latency.  Measured, 1024 to 2048 leaves
+// of 10x2, blocks of 1024 threads with LDS permutes and the split choices in the
+// same threads -> this: first pass 11.5 -> 6.1 us, second pass and choices 36
+// -> 6.1 us.
+constexpr int kPassBlock = 256;
+constexpr int kGroupWaves = kAnalysisBlock / 64;
+
+// scratch layout (doubles): per group the smallest shift, then per wavefront the
+// first pass's 4 + nx sums and the second pass's nx sums; then [sigma, z, 1/z^2,
+// C(r)]
+__device__ __forceinline__ size_t ngroups_of(uint32_t count)
 {
     return (static_cast<size_t>(count) + kAnalysisBlock - 1) / kAnalysisBlock;
 }
-
-// A block's sums of several terms in a fixed order: each term's wavefront
-// butterflies (wave_part), then, after one barrier, thread j adds term j's
-// wave sums in wave order (block_parts_out).
-constexpr int kAnalysisWaves = kAnalysisBlock / 64;
-__device__ __forceinline__ void wave_part(double v, double (*lds)[kAnalysisWaves], int j)
+__device__ __forceinline__ size_t nwaves_of(uint32_t count)
 {
-    const double s = dev::wave_sum(v);
-    if ((threadIdx.x & 63) == 0)
-        lds[j][threadIdx.x >> 6] = s;
+    return (static_cast<size_t>(count) + 63) / 64;
 }
-__device__ __forceinline__ void block_parts_out(const double (*lds)[kAnalysisWaves], int count,
-                                                double *part)
-{
-    if (static_cast<int>(threadIdx.x) < count) {
-        double t = 0.0;
-        for (int k = 0; k < kAnalysisWaves; ++k)
-            t += lds[threadIdx.x][k];
-        part[threadIdx.x] = t;
+struct Scratch {
+    double *shift, *first, *second, *scal;
+    __device__ __forceinline__ explicit Scratch(const LeafAnalysisArgs &a)
+    {
+        const size_t ng = ngroups_of(a.count), nw = nwaves_of(a.count);
+        shift = a.scratch;
+        first = shift + ng;
+        second = first + nw * (4 + a.nx);
+        scal = second + nw * a.nx;
     }
-}
+};
 
 __global__ void __launch_bounds__(kAnalysisBlock) shift_kernel(LeafAnalysisArgs a)
 {
@@ -153,16 +153,20 @@ __global__ void __launch_bounds__(kAnalysisBlock) shift_kernel(LeafAnalysisArgs 
         a.scratch[blockIdx.x] = m[0];
 }
 
+// The smallest shift of the groups; with DIRECT of the leaves themselves (short
+// lists: one launch less).
+template <bool DIRECT>
 __global__ void __launch_bounds__(kAnalysisBlock) shift_reduce_kernel(LeafAnalysisArgs a)
 {
     __shared__ double m[kAnalysisBlock];
-    const size_t nb = nblocks_of(a.count);
-    const int nx = a.nx;
-    double *scal = a.scratch + nb * (1 + 4 + 2 * nx);
+    const size_t n = DIRECT ? a.count : ngroups_of(a.count);
+    const int rec_len = 4 + 3 * a.nx;
     double sig = __builtin_inf();
-    for (size_t b = threadIdx.x; b < nb; b += kAnalysisBlock)
-        if (a.scratch[b] < sig)
-            sig = a.scratch[b];
+    for (size_t b = threadIdx.x; b < n; b += kAnalysisBlock) {
+        const double x = DIRECT ? a.rec[b * rec_len + 1] : a.scratch[b];
+        if (x < sig)
+            sig = x;
+    }
     m[threadIdx.x] = sig;
     __syncthreads();
     for (int k = kAnalysisBlock / 2; k > 0; k >>= 1) {
@@ -171,18 +175,19 @@ __global__ void __launch_bounds__(kAnalysisBlock) shift_reduce_kernel(LeafAnalys
         __syncthreads();
     }
     if (threadIdx.x == 0) {
-        scal[0] = m[0];
+        Scratch(a).scal[0] = m[0];
         a.out_totals[0] = m[0];
     }
 }
+constexpr uint32_t kDirectShift = 8 * kAnalysisBlock;
 
-__global__ void __launch_bounds__(kAnalysisBlock) first_pass_kernel(LeafAnalysisArgs a)
+__global__ void __launch_bounds__(kPassBlock) first_pass_kernel(LeafAnalysisArgs a)
 {
-    __shared__ double lds[4 + kMaxAnalysisNx][kAnalysisWaves];
-    const size_t nb = nblocks_of(a.count);
+    const Scratch sc(a);
     const int nx = a.nx, rec_len = 4 + 3 * nx, nt = 4 + nx;
-    const double sig = a.scratch[nb * (1 + 4 + 2 * nx)];
-    const uint32_t s = blockIdx.x * kAnalysisBlock + threadIdx.x;
+    const double sig = sc.scal[0];
+    const uint32_t s = blockIdx.x * kPassBlock + threadIdx.x;
+    const int lane = static_cast<int>(threadIdx.x & 63u);
     const bool on = s < a.count;
     const double *rec = a.rec + static_cast<size_t>(on ? s : 0) * rec_len;
     double n = 1.0, vol = 0.0, aa = 0.0, sw = 0.0, sw2 = 0.0;
@@ -193,8 +198,9 @@ __global__ void __launch_bounds__(kAnalysisBlock) first_pass_kernel(LeafAnalysis
         sw = aa * rec[2];
         sw2 = aa * aa * rec[3];
     }
-    double *part = a.scratch + nb + static_cast<size_t>(blockIdx.x) * nt;
-    // the finalize's sums: Z, Var Z, squared weights, samples, N(r)
+    // the finalize's sums: Z, Var Z, squared weights, samples, N(r); lane j keeps
+    // sum j
+    double mine = 0.0;
     for (int j = 0; j < nt; ++j) {
         double t = 0.0;
         if (on) {
@@ -209,93 +215,126 @@ __global__ void __launch_bounds__(kAnalysisBlock) first_pass_kernel(LeafAnalysis
             else
                 t = vol * aa * rec[j] / n;
         }
-        wave_part(t, lds, j);
+        const double v = dev::wave_sum(t);
+        mine = lane == j ? v : mine;
     }
-    __syncthreads();
-    block_parts_out(lds, nt, part);
+    const size_t wave = s >> 6;
+    if (lane < nt && wave < nwaves_of(a.count))
+        sc.first[wave * nt + lane] = mine;
 }
 
-// Neumaier sum of the blocks' partial sums in block order; thread j takes sum
-// j.  Loads go eight at a time ahead of their additions.
-__device__ double ordered_total(const double *part, size_t nb, int stride, int j)
+// Totals of `stride` sums from the wavefronts' (nw x stride): groups of
+// kGroupWaves in order, the groups with Neumaier compensation.  The block's 16
+// wavefronts take a group each, all its loads ahead of the additions, then
+// thread j adds the 16 groups' sums; total j is returned to thread j.
+constexpr int kMaxSums = 4 + kMaxAnalysisNx;
+__device__ double ordered_total(const double *part, size_t nw, int stride)
 {
-    constexpr size_t kBatch = 8;
+    __shared__ double sums[kGroupWaves][kMaxSums];
+    const int j = static_cast<int>(threadIdx.x & 63u);
+    const size_t mine = threadIdx.x >> 6, ng = (nw + kGroupWaves - 1) / kGroupWaves;
     double sum = 0.0, comp = 0.0;
-    for (size_t b0 = 0; b0 < nb; b0 += kBatch) {
-        double xb[kBatch];
+    for (size_t g0 = 0; g0 < ng; g0 += kGroupWaves) {
+        const size_t w0 = (g0 + mine) * kGroupWaves;
+        if (j < stride && w0 < nw) {
+            double x[kGroupWaves];
 #pragma unroll
-        for (size_t k = 0; k < kBatch; ++k)
-            xb[k] = b0 + k < nb ? part[(b0 + k) * stride + j] : 0.0;
+            for (int k = 0; k < kGroupWaves; ++k)
+                x[k] = w0 + k < nw ? part[(w0 + k) * stride + j] : 0.0;
+            double t = 0.0;
 #pragma unroll
-        for (size_t k = 0; k < kBatch; ++k) {
-            if (b0 + k < nb) {
-                const double x = xb[k];
+            for (int k = 0; k < kGroupWaves; ++k)
+                t += x[k];
+            sums[mine][j] = t;
+        }
+        __syncthreads();
+        if (threadIdx.x < static_cast<uint32_t>(stride)) {
+            for (size_t k = 0; k < kGroupWaves && g0 + k < ng; ++k) {
+                const double x = sums[k][j];
                 const double t = sum + x;
                 comp += fabs(sum) >= fabs(x) ? (sum - t) + x : (x - t) + sum;
                 sum = t;
             }
         }
+        __syncthreads();
     }
     return sum + comp;
 }
 
-__global__ void __launch_bounds__(64) first_reduce_kernel(LeafAnalysisArgs a)
+__global__ void __launch_bounds__(kAnalysisBlock) first_reduce_kernel(LeafAnalysisArgs a)
 {
-    __shared__ double tot[4 + kMaxAnalysisNx];
-    const size_t nb = nblocks_of(a.count);
-    const int nx = a.nx, nt = 4 + nx;
-    double *scal = a.scratch + nb * (1 + 4 + 2 * nx);
-    for (int j = threadIdx.x; j < nt; j += 64) {
-        tot[j] = ordered_total(a.scratch + nb, nb, nt, j);
-        a.out_totals[1 + j] = tot[j];
+    __shared__ double tot[kMaxSums];
+    const Scratch sc(a);
+    const int nx = a.nx, nt = 4 + nx, j = static_cast<int>(threadIdx.x);
+    const double t = ordered_total(sc.first, nwaves_of(a.count), nt);
+    if (j < nt) {
+        tot[j] = t;
+        a.out_totals[1 + j] = t;
     }
     __syncthreads();
-    if (threadIdx.x == 0) {
-        const double z = tot[0];
-        scal[1] = z;
-        scal[2] = z > 0 ? 1.0 / (z * z) : 0.0;
-        for (int r = 0; r < nx; ++r)
-            scal[3 + r] = tot[4 + r] / z;
+    const double z = tot[0];
+    if (j == 0) {
+        sc.scal[1] = z;
+        sc.scal[2] = z > 0 ? 1.0 / (z * z) : 0.0;
     }
+    if (j < nx)
+        sc.scal[3 + j] = tot[4 + j] / z;
 }
 
-// The leaf's split choice from its split statistics and the record of the
-// samples they cover (the host's split_choice).
-__device__ void split_choice(const double *sp, const double *base, int d, int32_t *best_out,
-                             double *gain_out)
+// A leaf's split choice from its split statistics and the record of the samples
+// they cover (the host's split_choice): lane j of half a wavefront takes
+// dimension j, the smallest spread wins, the lower dimension among equals.
+__device__ void split_choice(const LeafAnalysisArgs &a, uint32_t s, int j)
 {
+    const int d = a.d;
+    const double *sp = a.split + static_cast<size_t>(s) * (1 + 2 * d);
+    const double *base = a.base + static_cast<size_t>(s) * (4 + 3 * a.nx);
     const double S = base[2], Q = base[3], m = base[0], half = 0.5 * m;
-    const double v = Q / m - (S / m) * (S / m);
-    const double sigma = sqrt(v < 0.0 ? 0.0 : v);
     double best = __builtin_inf();
-    int best_j = 0;
-    for (int j = 0; j < d; ++j) {
+    if (j < d) {
         const double su = sp[1 + j], qu = sp[1 + d + j];
         const double sl = S - su, ql = Q - qu;
         const double vu0 = qu / half - (su / half) * (su / half);
         const double vl0 = ql / half - (sl / half) * (sl / half);
         const double vu = vu0 < 0.0 ? 0.0 : vu0, vl = vl0 < 0.0 ? 0.0 : vl0;
         const double sj = sqrt(vu) + sqrt(vl);
-        if (sj < best) {
-            best = sj;
-            best_j = j;
+        best = sj < best ? sj : best;  // (a NaN never wins)
+    }
+    int best_j = j;
+    for (int off = 16; off >= 1; off >>= 1) {
+        const double x = __shfl_xor(best, off, 32);
+        const int k = __shfl_xor(best_j, off, 32);
+        if (x < best || (x == best && k < best_j)) {
+            best = x;
+            best_j = k;
         }
     }
-    *best_out = best_j;
-    *gain_out = sigma > 0 ? best / (2.0 * sigma) : 1.0;
+    if (j == 0) {
+        const double v = Q / m - (S / m) * (S / m);
+        const double sigma = sqrt(v < 0.0 ? 0.0 : v);
+        a.best[s] = best_j;
+        a.gain[s] = sigma > 0 ? best / (2.0 * sigma) : 1.0;
+    }
 }
 
-__global__ void __launch_bounds__(kAnalysisBlock) second_pass_kernel(LeafAnalysisArgs a)
+// The first `sum_blocks` blocks sum the second pass, a thread per leaf; the
+// others make the split choices, half a wavefront per leaf.
+__global__ void __launch_bounds__(kPassBlock) second_pass_kernel(LeafAnalysisArgs a,
+                                                                 uint32_t sum_blocks)
 {
-    __shared__ double lds[kMaxAnalysisNx][kAnalysisWaves];
-    const size_t nb = nblocks_of(a.count);
-    const int nx = a.nx, d = a.d, rec_len = 4 + 3 * nx, split_len = 1 + 2 * d;
-    const double *scal = a.scratch + nb * (1 + 4 + 2 * nx);
-    const double sig = scal[0], inv_z2 = scal[2];
-    const uint32_t s = blockIdx.x * kAnalysisBlock + threadIdx.x;
+    const int lane = static_cast<int>(threadIdx.x & 63u);
+    if (blockIdx.x >= sum_blocks) {
+        const uint32_t s = ((blockIdx.x - sum_blocks) * kPassBlock + threadIdx.x) >> 5;
+        if (s < a.count)
+            split_choice(a, s, lane & 31);
+        return;
+    }
+    const Scratch sc(a);
+    const int nx = a.nx, rec_len = 4 + 3 * nx;
+    const double sig = sc.scal[0], inv_z2 = sc.scal[2];
+    const uint32_t s = blockIdx.x * kPassBlock + threadIdx.x;
     const bool on = s < a.count;
     const double *rec = a.rec + static_cast<size_t>(on ? s : 0) * rec_len;
-    double *part = a.scratch + nb * (1 + 4 + nx) + static_cast<size_t>(blockIdx.x) * nx;
     double n = 1.0, v2 = 0.0, nn = 1.0, aa = 0.0, a2 = 0.0, sw = 0.0, var_z = 0.0;
     if (on) {
         n = rec[0];
@@ -308,11 +347,11 @@ __global__ void __launch_bounds__(kAnalysisBlock) second_pass_kernel(LeafAnalysi
         const double sw2 = a2 * rec[3];
         var_z = v2 * (sw2 - sw * sw / n) / nn;
     }
-    double e = 0.0;
+    double e = 0.0, mine = 0.0;
     for (int r = 0; r < nx; ++r) {
         double t = 0.0;
         if (on) {
-            const double C = scal[3 + r];
+            const double C = sc.scal[3 + r];
             const double spw = aa * rec[4 + r], spw2 = a2 * rec[4 + nx + r],
                          spww = a2 * rec[4 + 2 * nx + r];
             const double var_n = v2 * (spw2 - spw * spw / n) / nn;
@@ -320,25 +359,24 @@ __global__ void __launch_bounds__(kAnalysisBlock) second_pass_kernel(LeafAnalysi
             t = var_n - 2.0 * C * cov + C * C * var_z;
             e += t;
         }
-        wave_part(t, lds, r);
+        const double v = dev::wave_sum(t);
+        mine = lane == r ? v : mine;
     }
-    __syncthreads();
-    block_parts_out(lds, nx, part);
+    const size_t wave = s >> 6;
+    if (lane < nx && wave < nwaves_of(a.count))
+        sc.second[wave * nx + lane] = mine;
     if (!on)
         return;
     // the host's max(e, 0) / Z^2, read back as a contribution (NaN counts 0)
     const double c = (e < 0.0 ? 0.0 : e) * inv_z2;
     a.e[s] = c >= 0.0 ? c : 0.0;
-    split_choice(a.split + static_cast<size_t>(s) * split_len,
-                 a.base + static_cast<size_t>(s) * rec_len, d, &a.best[s], &a.gain[s]);
 }
 
-__global__ void __launch_bounds__(64) second_reduce_kernel(LeafAnalysisArgs a)
+__global__ void __launch_bounds__(kAnalysisBlock) second_reduce_kernel(LeafAnalysisArgs a)
 {
-    const size_t nb = nblocks_of(a.count);
-    const int nx = a.nx;
-    for (int r = threadIdx.x; r < nx; r += 64)
-        a.out_totals[1 + 4 + nx + r] = ordered_total(a.scratch + nb * (1 + 4 + nx), nb, nx, r);
+    const double t = ordered_total(Scratch(a).second, nwaves_of(a.count), a.nx);
+    if (static_cast<int>(threadIdx.x) < a.nx)
+        a.out_totals[1 + 4 + a.nx + threadIdx.x] = t;
 }
 
 }  // namespace
@@ -349,29 +387,40 @@ hipError_t launch_fold(const FoldArgs &args, hipStream_t stream)
         return hipSuccess;
     if (args.nx < 1 || args.nx > kMaxAnalysisNx || args.d < 1 || args.d > 32)
         return hipErrorInvalidValue;
-    const uint32_t grid = (args.count + kFoldBlock - 1) / kFoldBlock;
-    hipLaunchKernelGGL(fold_kernel, dim3(grid), dim3(kFoldBlock), 0, stream, args);
+    const size_t grid = (static_cast<size_t>(args.count) * 64 + kFoldBlock - 1) / kFoldBlock;
+    hipLaunchKernelGGL(fold_kernel, dim3(static_cast<uint32_t>(grid)), dim3(kFoldBlock), 0, stream, args);
     return hipGetLastError();
 }
 
 size_t analysis_scratch_doubles(uint32_t count, int nx)
 {
-    const size_t nb = (static_cast<size_t>(count) + kAnalysisBlock - 1) / kAnalysisBlock;
-    return nb * (1 + 4 + 2 * static_cast<size_t>(nx)) + 3 + static_cast<size_t>(nx);
+    const size_t ng = (static_cast<size_t>(count) + kAnalysisBlock - 1) / kAnalysisBlock;
+    const size_t nw = (static_cast<size_t>(count) + 63) / 64;
+    return ng + nw * (4 + 2 * static_cast<size_t>(nx)) + 3 + static_cast<size_t>(nx);
 }
 
 hipError_t launch_leaf_analysis(const LeafAnalysisArgs &args, hipStream_t stream)
 {
     if (args.count == 0 || args.nx < 1 || args.nx > kMaxAnalysisNx || args.d < 1 || args.d > 32)
         return hipErrorInvalidValue;
-    const uint32_t grid = static_cast<uint32_t>(
-        (static_cast<size_t>(args.count) + kAnalysisBlock - 1) / kAnalysisBlock);
-    hipLaunchKernelGGL(shift_kernel, dim3(grid), dim3(kAnalysisBlock), 0, stream, args);
-    hipLaunchKernelGGL(shift_reduce_kernel, dim3(1), dim3(kAnalysisBlock), 0, stream, args);
-    hipLaunchKernelGGL(first_pass_kernel, dim3(grid), dim3(kAnalysisBlock), 0, stream, args);
-    hipLaunchKernelGGL(first_reduce_kernel, dim3(1), dim3(64), 0, stream, args);
-    hipLaunchKernelGGL(second_pass_kernel, dim3(grid), dim3(kAnalysisBlock), 0, stream, args);
-    hipLaunchKernelGGL(second_reduce_kernel, dim3(1), dim3(64), 0, stream, args);
+    auto blocks = [&](size_t threads, size_t block) {
+        return static_cast<uint32_t>((threads + block - 1) / block);
+    };
+    const size_t count = args.count;
+    if (args.count <= kDirectShift) {
+        hipLaunchKernelGGL(shift_reduce_kernel<true>, dim3(1), dim3(kAnalysisBlock), 0, stream, args);
+    } else {
+        hipLaunchKernelGGL(shift_kernel, dim3(blocks(count, kAnalysisBlock)), dim3(kAnalysisBlock), 0,
+                           stream, args);
+        hipLaunchKernelGGL(shift_reduce_kernel<false>, dim3(1), dim3(kAnalysisBlock), 0, stream,
+                           args);
+    }
+    const uint32_t sums = blocks(count, kPassBlock), choices = blocks(32 * count, kPassBlock);
+    hipLaunchKernelGGL(first_pass_kernel, dim3(sums), dim3(kPassBlock), 0, stream, args);
+    hipLaunchKernelGGL(first_reduce_kernel, dim3(1), dim3(kAnalysisBlock), 0, stream, args);
+    hipLaunchKernelGGL(second_pass_kernel, dim3(sums + choices), dim3(kPassBlock), 0, stream, args,
+                       sums);
+    hipLaunchKernelGGL(second_reduce_kernel, dim3(1), dim3(kAnalysisBlock), 0, stream, args);
     return hipGetLastError();
 }
 

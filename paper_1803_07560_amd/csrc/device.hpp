@@ -411,12 +411,13 @@ __device__ __forceinline__ double row_rotate(double x)
     return row_move<0x120 + R>(x);
 }
 
-// One halving step of a many-field wavefront sum: the lanes of the first half
-// (of the wavefront for ROWS = 2, of each pair of rows for ROWS = 1) go on with
-// field a, those of the second half with field b, each holding its own value
-// plus its partner lane's.  The swap exchanges a's second half with b's first.
+// One halving exchange: the lanes of the first half (of the wavefront for ROWS =
+// 2, of each pair of rows for ROWS = 1) go on with field a, those of the second
+// half with field b; `first` and `second` become the values that the partner
+// lanes in the first and in the second half hold of the lane's field.  The swap
+// exchanges a's second half with b's first.
 template <int ROWS>
-__device__ __forceinline__ double halve(double a, double b)
+__device__ __forceinline__ void exchange(double a, double b, double &first, double &second)
 {
     const uint64_t x = __builtin_bit_cast(uint64_t, a), y = __builtin_bit_cast(uint64_t, b);
     const uint32_t xl = static_cast<uint32_t>(x), xh = static_cast<uint32_t>(x >> 32);
@@ -425,8 +426,17 @@ __device__ __forceinline__ double halve(double a, double b)
                               : __builtin_amdgcn_permlane16_swap(xl, yl, false, false);
     const auto hi = ROWS == 2 ? __builtin_amdgcn_permlane32_swap(xh, yh, false, false)
                               : __builtin_amdgcn_permlane16_swap(xh, yh, false, false);
-    return __builtin_bit_cast(double, static_cast<uint64_t>(hi[0]) << 32 | lo[0]) +
-           __builtin_bit_cast(double, static_cast<uint64_t>(hi[1]) << 32 | lo[1]);
+    first = __builtin_bit_cast(double, static_cast<uint64_t>(hi[0]) << 32 | lo[0]);
+    second = __builtin_bit_cast(double, static_cast<uint64_t>(hi[1]) << 32 | lo[1]);
+}
+// One halving step of a many-field wavefront sum: field a or b over both partner
+// lanes.
+template <int ROWS>
+__device__ __forceinline__ double halve(double a, double b)
+{
+    double x, y;
+    exchange<ROWS>(a, b, x, y);
+    return x + y;
 }
 
 // Butterfly sum across the 64 lanes of a wavefront (lane distances 32, 16, 8, 4, 2,
@@ -455,18 +465,15 @@ __device__ __forceinline__ double wave_sum(double v)
 // form, 2^16 .. 2^22 evaluations each) 1.50 -> 1.42 ms, 2^27 evaluations of 8x2
 // as FP64 pairs (128 items a CU) 1.052 -> 1.037 ms, a 4x2 call of 2^16
 // evaluations 238 -> 225 us; items of 1024 samples per thread the same.
-template <int N, class Value>
-__device__ __forceinline__ void wave_sums(Value &&value, double *out, uint32_t lane)
+template <int N, class Pair>
+__device__ __forceinline__ void wave_sums_of(Pair &&pair, double *out, uint32_t lane)
 {
     constexpr int Q = (N + 3) / 4, H = 2 * Q;
     const uint32_t row = lane >> 4;
     const int first = static_cast<int>((row & 1) * Q + (row >> 1) * H);
-    auto field = [&](int i) { return i < N ? value(i) : 0.0; };
 #pragma unroll
     for (int q = 0; q < Q; ++q) {
-        const double a = halve<2>(field(q), field(q + H));
-        const double b = halve<2>(field(q + Q), field(q + H + Q));
-        double v = halve<1>(a, b);
+        double v = halve<1>(pair(q, q + H), pair(q + Q, q + H + Q));
         v += row_rotate<8>(v);
         v += row_rotate<4>(v);
         v += row_rotate<2>(v);
@@ -474,6 +481,39 @@ __device__ __forceinline__ void wave_sums(Value &&value, double *out, uint32_t l
         if ((lane & 15u) == 0 && first + q < N)
             out[first + q] = v;
     }
+}
+
+template <int N, class Value>
+__device__ __forceinline__ void wave_sums(Value &&value, double *out, uint32_t lane)
+{
+    auto field = [&](int i) { return i < N ? value(i) : 0.0; };
+    wave_sums_of<N>([&](int i, int j) { return halve<2>(field(i), field(j)); }, out, lane);
+}
+// The same of fields that are first scaled by f1 (order(i) = 1), its square (2) or
+// not at all (0), each lane by its own factor: the lane pairs' sums are one
+// rounded product plus the other in a fused multiply-add, the first half's lane
+// fused.  (What the compiler made of a multiplication before a butterfly; a run
+// whose decisions hang on the last bits of these sums goes the same way.)
+template <int N, class Value, class Order>
+__device__ __forceinline__ void wave_sums_scaled(Value &&value, Order &&order, double f1,
+                                                 double *out, uint32_t lane)
+{
+    auto field = [&](int i) { return i < N ? value(i) : 0.0; };
+    double fa[3] = {1.0, 0.0, 0.0}, fb[3] = {1.0, 0.0, 0.0};
+    exchange<2>(f1, f1, fa[1], fb[1]);
+    fa[2] = fa[1] * fa[1];
+    fb[2] = fb[1] * fb[1];
+    wave_sums_of<N>(
+        [&](int i, int j) {
+            double x, y;
+            exchange<2>(field(i), field(j), x, y);
+            const int oi = i < N ? order(i) : 0, oj = j < N ? order(j) : 0;
+            const bool low = lane < 32;
+            const double fx = oi == oj ? fa[oi] : low ? fa[oi] : fa[oj];
+            const double fy = oi == oj ? fb[oi] : low ? fb[oi] : fb[oj];
+            return __fma_rn(x, fx, __dmul_rn(y, fy));
+        },
+        out, lane);
 }
 
 __device__ __forceinline__ float wave_min(float v)

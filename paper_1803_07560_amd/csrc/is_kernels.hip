@@ -486,11 +486,15 @@ __global__ void __launch_bounds__(BLOCK)
         float wave_sigma = 0.0f;
         if constexpr (PREC != kFP64) {
             wave_sigma = dev::wave_min(sigma);
-            rescale(sigma == __builtin_inff()
-                        ? 0.0
-                        : exp(static_cast<double>(wave_sigma) - static_cast<double>(sigma)));
+            const double f1 = sigma == __builtin_inff()
+                                  ? 0.0
+                                  : exp(static_cast<double>(wave_sigma) - static_cast<double>(sigma));
+            dev::wave_sums_scaled<NF>(
+                [&](int i) { return acc[i]; },
+                [](int i) { return i == 0 || (i >= 2 && i < 2 + NR) ? 1 : 2; }, f1, red[wave], lane);
+        } else {
+            dev::wave_sums<NF>([&](int i) { return acc[i]; }, red[wave], lane);
         }
-        dev::wave_sums<NF>([&](int i) { return acc[i]; }, red[wave], lane);
         if (lane == 0)
             red_sigma[wave] = wave_sigma;
         __syncthreads();

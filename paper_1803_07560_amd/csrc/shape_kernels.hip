@@ -229,12 +229,9 @@ __global__ void __launch_bounds__(BLOCK)
         Sig sigma = PREC == kFP64Shifted ? static_cast<Sig>(__DBL_MAX__)
                                          : static_cast<Sig>(__builtin_inff());
 
-        auto rescale = [&](double f1) {
-            const double f2 = f1 * f1;
-#pragma unroll
-            for (int i = 0; i < NA; ++i)
-                acc[i] *= F::order(i) == 1 ? f1 : f2;
+        auto rescale_split32 = [&](double f1) {
             if constexpr (kSplit32) {
+                const double f2 = f1 * f1;
                 // in FP64: f2 can lie below FP32's range while the product does not
 #pragma unroll
                 for (int k = 0; k < D; ++k) {
@@ -242,6 +239,13 @@ __global__ void __launch_bounds__(BLOCK)
                     sacc[D + k] = static_cast<float>(static_cast<double>(sacc[D + k]) * f2);
                 }
             }
+        };
+        auto rescale = [&](double f1) {
+            const double f2 = f1 * f1;
+#pragma unroll
+            for (int i = 0; i < NA; ++i)
+                acc[i] *= F::order(i) == 1 ? f1 : f2;
+            rescale_split32(f1);
         };
         // accumulated field i as an FP64 value in the record's scale
         auto acc_value = [&](int i) -> double {
@@ -586,11 +590,16 @@ __global__ void __launch_bounds__(BLOCK)
         if constexpr (kShifted) {
             wave_sigma = dev::wave_min(sigma);
             // lanes that took no sample hold sigma = inf and zero sums
-            rescale(sigma == static_cast<Sig>(__builtin_inff())
-                        ? 0.0
-                        : exp(static_cast<double>(wave_sigma) - static_cast<double>(sigma)));
+            const double f1 = sigma == static_cast<Sig>(__builtin_inff())
+                                  ? 0.0
+                                  : exp(static_cast<double>(wave_sigma) - static_cast<double>(sigma));
+            rescale_split32(f1);
+            dev::wave_sums_scaled<NF>([&](int i) { return acc_value(i); },
+                                      [](int i) { return kSplit32 && i >= F::kMain ? 0 : F::order(i); },
+                                      f1, red[wave], lane);
+        } else {
+            dev::wave_sums<NF>([&](int i) { return acc_value(i); }, red[wave], lane);
         }
-        dev::wave_sums<NF>([&](int i) { return acc_value(i); }, red[wave], lane);
         if (lane == 0)
             red_sigma[wave] = wave_sigma;
         __syncthreads();

@@ -2,15 +2,18 @@
 // adaptive refinement): device buffers and pinned host staging sized once and
 // grown geometrically, the whole device sequence captured in a hipGraph.
 //
-// One call: the list staged in pinned memory is copied to the device, the
-// point maps and work items are built there (launch_build_items), the queue
-// head is reset, the persistent Monte Carlo kernel drains the items, the merge
-// kernel folds them into per-entry records, and the records (and split
+// One call: the list staged in pinned memory is copied to the device (one block,
+// the zeroed queue head in it), the point maps and work items are built there
+// (launch_build_items), the persistent Monte Carlo kernel drains the items, the
+// merge kernel folds them into per-entry records, and the records (and split
 // statistics) are copied back to pinned memory.  That sequence is captured on
 // the context's stream and applied to the executable graph of the previous
 // call with hipGraphExecUpdate (same nodes, new sizes and arguments); only when
 // the update is refused is the graph instantiated again.  No device allocation
-// happens unless a list outgrows every list before it.
+// happens unless a list outgrows every list before it.  (Six arrays copied apart
+// and a kernel that reset the queue head cost each of a round's two replays some
+// 30 us, and each run the pinning of twice eight buffers: a run of 2^28
+// evaluations over 8 rounds 9.7 -> 8.2 ms without them.)
 #include "runtime.h"
 
 #include <algorithm>
@@ -39,27 +42,42 @@ hipError_t grow_device(T **p, size_t *cap, size_t need)
     return e;
 }
 
-// Pinned staging keeps its contents when it grows (entries are appended).
+// Pinned memory; its contents are dropped when it grows.
 template <class T>
-hipError_t grow_pinned(T **p, size_t *cap, size_t used, size_t need)
+hipError_t grow_pinned(T **p, size_t *cap, size_t need)
 {
     if (need <= *cap && *p)
         return hipSuccess;
     const size_t n = std::max<size_t>({need, 2 * *cap, 64});
-    T *q = nullptr;
-    hipError_t e = hipHostMalloc(reinterpret_cast<void **>(&q), n * sizeof(T), hipHostMallocDefault);
-    if (e != hipSuccess)
-        return e;
-    if (*p) {
-        std::memcpy(q, *p, used * sizeof(T));
+    if (*p)
         (void)hipHostFree(*p);
-    }
-    *p = q;
-    *cap = n;
-    return hipSuccess;
+    *p = nullptr;
+    *cap = 0;
+    hipError_t e = hipHostMalloc(reinterpret_cast<void **>(p), n * sizeof(T), hipHostMallocDefault);
+    if (e == hipSuccess)
+        *cap = n;
+    return e;
 }
 
 }  // namespace
+
+ResidentEval::Staged::Staged(size_t count, int d)
+{
+    size_t at = 0;
+    auto region = [&](size_t size) {
+        const size_t here = at;
+        at += (size + 255) & ~size_t(255);
+        return here;
+    };
+    region(sizeof(EvalParams));
+    head = region(sizeof(uint32_t));
+    id = region(count * 8);
+    n = region(count * 8);
+    off = region(count * 8);
+    lo = region(count * static_cast<size_t>(d) * 8);
+    hi = region(count * static_cast<size_t>(d) * 8);
+    bytes = at;
+}
 
 ResidentEval::~ResidentEval() { release(); }
 
@@ -74,13 +92,12 @@ void ResidentEval::release()
     exec_ = nullptr;
     prepared_ = 0;
     launched_ = false;
-    void *dev[] = {d_id_, d_n_, d_off_, d_lo_, d_hi_, d_base64_, d_scale64_, d_base32_, d_scale32_,
-                   d_params_, d_sub_first_, d_items_, d_item_rec_, d_item_split_, d_sub_rec_,
-                   d_sub_split_, d_head_};
+    void *dev[] = {d_stage_, d_base64_, d_scale64_, d_base32_, d_scale32_, d_sub_first_, d_items_,
+                   d_item_rec_, d_item_split_, d_sub_rec_, d_sub_split_};
     for (void *p : dev)
         if (p)
             (void)hipFree(p);
-    void *host[] = {h_id_, h_n_, h_off_, h_lo_, h_hi_, h_rec_, h_split_, h_params_};
+    void *host[] = {h_stage_, h_rec_, h_split_};
     if (ev_start_)
         (void)hipEventDestroy(ev_start_);
     if (ev_stop_)
@@ -89,17 +106,14 @@ void ResidentEval::release()
     for (void *p : host)
         if (p)
             (void)hipHostFree(p);
-    d_id_ = d_n_ = d_off_ = nullptr;
-    d_lo_ = d_hi_ = d_base64_ = d_scale64_ = nullptr;
+    h_stage_ = d_stage_ = nullptr;
+    h_id_ = h_n_ = h_off_ = nullptr;
+    h_lo_ = h_hi_ = h_rec_ = h_split_ = nullptr;
+    d_base64_ = d_scale64_ = nullptr;
     d_base32_ = d_scale32_ = nullptr;
-    d_params_ = nullptr;
     d_sub_first_ = nullptr;
     d_items_ = nullptr;
     d_item_rec_ = d_item_split_ = d_sub_rec_ = d_sub_split_ = nullptr;
-    d_head_ = nullptr;
-    h_id_ = h_n_ = h_off_ = nullptr;
-    h_lo_ = h_hi_ = h_rec_ = h_split_ = nullptr;
-    h_params_ = nullptr;
 }
 
 bfi_status ResidentEval::init(bfi_context *ctx, const bfi_lattice &lat, int prec, bool split,
@@ -126,53 +140,21 @@ bfi_status ResidentEval::init(bfi_context *ctx, const bfi_lattice &lat, int prec
     BFI_HIP(kernel_info(lat.nx, lat.nt, spec, &info));
     resident_blocks_ = static_cast<uint64_t>(std::max(info.blocks_per_cu, 1)) *
                        std::max(ctx->cu_count, 1);
-    BFI_HIP(grow_pinned(&h_params_, &cap_params_, 0, 1));
-    BFI_HIP(grow_device(&d_params_, &cap_dparams_, 1));
-    BFI_HIP(grow_device(&d_head_, &cap_head_, 1));
     count_ = 0;
-    return BFI_OK;
-}
-
-bfi_status ResidentEval::reserve(size_t count)
-{
-    if (count <= cap_h_sub_ && h_id_)
-        return BFI_OK;
-    const size_t n = std::max<size_t>({count, 2 * cap_h_sub_, 64});
-    const size_t d = static_cast<size_t>(d_);
-    size_t c = cap_h_sub_;
-    BFI_HIP(grow_pinned(&h_id_, &c, count_, n));
-    c = cap_h_sub_;
-    BFI_HIP(grow_pinned(&h_n_, &c, count_, n));
-    c = cap_h_sub_;
-    BFI_HIP(grow_pinned(&h_off_, &c, count_, n));
-    c = cap_h_sub_ * d;
-    BFI_HIP(grow_pinned(&h_lo_, &c, count_ * d, n * d));
-    c = cap_h_sub_ * d;
-    BFI_HIP(grow_pinned(&h_hi_, &c, count_ * d, n * d));
-    cap_h_sub_ = n;
     return BFI_OK;
 }
 
 bfi_status ResidentEval::stage(size_t count)
 {
     count_ = 0;
-    BFI_TRY(reserve(count));
+    const Staged at(count, d_);
+    BFI_HIP(grow_pinned(&h_stage_, &cap_h_stage_, at.bytes));
+    h_id_ = reinterpret_cast<uint64_t *>(h_stage_ + at.id);
+    h_n_ = reinterpret_cast<uint64_t *>(h_stage_ + at.n);
+    h_off_ = reinterpret_cast<uint64_t *>(h_stage_ + at.off);
+    h_lo_ = reinterpret_cast<double *>(h_stage_ + at.lo);
+    h_hi_ = reinterpret_cast<double *>(h_stage_ + at.hi);
     count_ = count;
-    return BFI_OK;
-}
-
-bfi_status ResidentEval::push(uint64_t id, uint64_t offset, uint64_t n, const double *lo,
-                              const double *hi)
-{
-    if (count_ + 1 > cap_h_sub_ || !h_id_)
-        BFI_TRY(reserve(count_ + 1));
-    const size_t d = static_cast<size_t>(d_);
-    h_id_[count_] = id;
-    h_off_[count_] = offset;
-    h_n_[count_] = n;
-    std::memcpy(h_lo_ + count_ * d, lo, d * sizeof(double));
-    std::memcpy(h_hi_ + count_ * d, hi, d * sizeof(double));
-    ++count_;
     return BFI_OK;
 }
 
@@ -200,32 +182,32 @@ bfi_status ResidentEval::prepare(uint64_t seed)
     }
     // device capacity (a buffer that moves is a new argument of its nodes, which
     // the graph update below takes like any other)
-    BFI_HIP(grow_device(&d_id_, &cap_d_sub_[0], nsub));
-    BFI_HIP(grow_device(&d_n_, &cap_d_sub_[1], nsub));
-    BFI_HIP(grow_device(&d_off_, &cap_d_sub_[2], nsub));
-    BFI_HIP(grow_device(&d_sub_first_, &cap_d_sub_[3], nsub + 1));
-    BFI_HIP(grow_device(&d_lo_, &cap_d_map_[0], nsub * d));
-    BFI_HIP(grow_device(&d_hi_, &cap_d_map_[1], nsub * d));
-    BFI_HIP(grow_device(&d_base64_, &cap_d_map_[2], nsub * d));
-    BFI_HIP(grow_device(&d_scale64_, &cap_d_map_[3], nsub * d));
-    BFI_HIP(grow_device(&d_base32_, &cap_d_map_[4], nsub * d));
-    BFI_HIP(grow_device(&d_scale32_, &cap_d_map_[5], nsub * d));
+    const Staged at(nsub, d_);
+    BFI_HIP(grow_device(&d_stage_, &cap_d_stage_, at.bytes));
+    BFI_HIP(grow_device(&d_sub_first_, &cap_d_sub_[0], nsub + 1));
+    BFI_HIP(grow_device(&d_base64_, &cap_d_map_[0], nsub * d));
+    BFI_HIP(grow_device(&d_scale64_, &cap_d_map_[1], nsub * d));
+    BFI_HIP(grow_device(&d_base32_, &cap_d_map_[2], nsub * d));
+    BFI_HIP(grow_device(&d_scale32_, &cap_d_map_[3], nsub * d));
     BFI_HIP(grow_device(&d_items_, &cap_d_items_[0], nitems));
     BFI_HIP(grow_device(&d_item_rec_, &cap_d_items_[1], nitems * rec_len_));
-    BFI_HIP(grow_device(&d_sub_rec_, &cap_d_sub_[4], nsub * rec_len_));
+    BFI_HIP(grow_device(&d_sub_rec_, &cap_d_sub_[1], nsub * rec_len_));
     // pinned room for the records only when they come back (at a million
     // leaves that is hundreds of megabytes, slow to pin)
     if (copy_records_)
-        BFI_HIP(grow_pinned(&h_rec_, &cap_h_rec_, 0, nsub * rec_len_));
+        BFI_HIP(grow_pinned(&h_rec_, &cap_h_rec_, nsub * rec_len_));
     if (split_) {
         BFI_HIP(grow_device(&d_item_split_, &cap_d_items_[2], nitems * 2 * d));
-        BFI_HIP(grow_device(&d_sub_split_, &cap_d_sub_[5], nsub * split_len_));
+        BFI_HIP(grow_device(&d_sub_split_, &cap_d_sub_[2], nsub * split_len_));
         if (copy_records_)
-            BFI_HIP(grow_pinned(&h_split_, &cap_h_split_, 0, nsub * split_len_));
+            BFI_HIP(grow_pinned(&h_split_, &cap_h_split_, nsub * split_len_));
     }
-    *h_params_ = EvalParams{d_base64_, d_scale64_, d_base32_, d_scale32_, d_id_, d_off_,
-                            make_coef(lat_), static_cast<uint32_t>(seed),
-                            static_cast<uint32_t>(seed >> 32)};
+    const EvalParams P{d_base64_, d_scale64_, d_base32_, d_scale32_,
+                       reinterpret_cast<const uint64_t *>(d_stage_ + at.id),
+                       reinterpret_cast<const uint64_t *>(d_stage_ + at.off), make_coef(lat_),
+                       static_cast<uint32_t>(seed), static_cast<uint32_t>(seed >> 32)};
+    std::memcpy(h_stage_, &P, sizeof(P));
+    std::memset(h_stage_ + at.head, 0, sizeof(uint32_t));
 
     hipStream_t st = ctx_->stream;
     BFI_HIP(hipStreamBeginCapture(st, hipStreamCaptureModeThreadLocal));
@@ -312,18 +294,15 @@ bfi_status ResidentEval::finish(double *rec_out, double *split_out, double *devi
 
 bfi_status ResidentEval::enqueue(size_t nsub, uint64_t nitems, hipStream_t st)
 {
-    const size_t d = static_cast<size_t>(d_);
-    BFI_HIP(hipMemcpyAsync(d_id_, h_id_, nsub * 8, hipMemcpyHostToDevice, st));
-    BFI_HIP(hipMemcpyAsync(d_n_, h_n_, nsub * 8, hipMemcpyHostToDevice, st));
-    BFI_HIP(hipMemcpyAsync(d_off_, h_off_, nsub * 8, hipMemcpyHostToDevice, st));
-    BFI_HIP(hipMemcpyAsync(d_lo_, h_lo_, nsub * d * 8, hipMemcpyHostToDevice, st));
-    BFI_HIP(hipMemcpyAsync(d_hi_, h_hi_, nsub * d * 8, hipMemcpyHostToDevice, st));
-    BFI_HIP(hipMemcpyAsync(d_params_, h_params_, sizeof(EvalParams), hipMemcpyHostToDevice, st));
-    BuildArgs ba{d_lo_, d_hi_, d_n_, d_sub_first_, d_base64_, d_scale64_, d_base32_, d_scale32_,
-                 d_items_, d_params_, d_item_rec_, chunk_, static_cast<uint32_t>(nsub), d_,
-                 rec_len_};
+    const Staged at(nsub, d_);
+    auto *params = reinterpret_cast<EvalParams *>(d_stage_);
+    BFI_HIP(hipMemcpyAsync(d_stage_, h_stage_, at.bytes, hipMemcpyHostToDevice, st));
+    BuildArgs ba{reinterpret_cast<const double *>(d_stage_ + at.lo),
+                 reinterpret_cast<const double *>(d_stage_ + at.hi),
+                 reinterpret_cast<const uint64_t *>(d_stage_ + at.n), d_sub_first_, d_base64_,
+                 d_scale64_, d_base32_, d_scale32_, d_items_, params, d_item_rec_, chunk_,
+                 static_cast<uint32_t>(nsub), d_, rec_len_};
     BFI_HIP(launch_build_items(ba, st));
-    BFI_HIP(launch_reset_head(d_head_, st));
     LaunchSpec spec{prec_, launch_.block, split_ ? 1 : 0, 1,
                     static_cast<uint32_t>(std::min<uint64_t>(resident_blocks_, nitems)),
                     lat_.observable, lat_.antithetic};
@@ -331,7 +310,7 @@ bfi_status ResidentEval::enqueue(size_t nsub, uint64_t nitems, hipStream_t st)
     a.items = d_items_;
     a.item_rec = d_item_rec_;
     a.item_split = split_ ? d_item_split_ : nullptr;
-    a.queue_head = d_head_;
+    a.queue_head = reinterpret_cast<uint32_t *>(d_stage_ + at.head);
     a.nitems = static_cast<uint32_t>(nitems);
     a.samples_per_thread = static_cast<uint32_t>(launch_.samples_per_thread);
     BFI_HIP(launch_mc(lat_.nx, lat_.nt, spec, a, st));

@@ -188,7 +188,7 @@ bfi_status finalize_records(int nx, int d, size_t nsub, const double *lo, const 
                             double *leaf_var = nullptr, const double *volumes = nullptr);
 
 // Evaluates work lists that change from call to call (adaptive rounds) with
-// resident buffers: entries are pushed into pinned staging, run() uploads them,
+// resident buffers: entries are written into pinned staging, run() uploads them,
 // builds items and point maps on the device, drains them with the persistent
 // kernel, merges and downloads one record (and split statistics) per entry,
 // all as one captured graph updated in place from call to call.  Buffers grow
@@ -203,11 +203,9 @@ public:
     // split: accumulate split statistics (256-thread blocks, d <= 32)
     bfi_status init(bfi_context *ctx, const bfi_lattice &lat, int prec, bool split,
                     const bfi_launch *launch);
-    bfi_status reserve(size_t count);
-    // append one entry: samples [offset, offset + n) of stream `id` over [lo, hi)
-    bfi_status push(uint64_t id, uint64_t offset, uint64_t n, const double *lo, const double *hi);
-    // bulk form: stage(count) sizes the list, then set() fills entry i (entries
-    // may be set from several threads)
+    // stage(count) sizes the list, then set() fills entry i: samples [offset,
+    // offset + n) of stream `id` over [lo, hi) (entries may be set from several
+    // threads)
     bfi_status stage(size_t count);
     void set(size_t i, uint64_t id, uint64_t offset, uint64_t n, const double *lo,
              const double *hi)
@@ -268,22 +266,28 @@ private:
     bfi_launch launch_{};
     uint64_t chunk_ = 0, resident_blocks_ = 0;
     size_t count_ = 0;
-    // pinned staging
+    // What the host writes for a list, one block in pinned memory and its copy in
+    // device memory: parameters, queue head (0), then ids, counts, offsets and the
+    // boxes, each from a multiple of 256 bytes.
+    struct Staged {
+        size_t head, id, n, off, lo, hi, bytes;
+        Staged(size_t count, int d);
+    };
+    char *h_stage_ = nullptr, *d_stage_ = nullptr;
+    size_t cap_h_stage_ = 0, cap_d_stage_ = 0;
+    // pieces of h_stage_ for the staged count
     uint64_t *h_id_ = nullptr, *h_n_ = nullptr, *h_off_ = nullptr;
-    double *h_lo_ = nullptr, *h_hi_ = nullptr, *h_rec_ = nullptr, *h_split_ = nullptr;
-    EvalParams *h_params_ = nullptr;
-    size_t cap_h_sub_ = 0, cap_h_rec_ = 0, cap_h_split_ = 0, cap_params_ = 0;
+    double *h_lo_ = nullptr, *h_hi_ = nullptr;
+    double *h_rec_ = nullptr, *h_split_ = nullptr;
+    size_t cap_h_rec_ = 0, cap_h_split_ = 0;
     // device
-    uint64_t *d_id_ = nullptr, *d_n_ = nullptr, *d_off_ = nullptr;
-    double *d_lo_ = nullptr, *d_hi_ = nullptr, *d_base64_ = nullptr, *d_scale64_ = nullptr;
+    double *d_base64_ = nullptr, *d_scale64_ = nullptr;
     float *d_base32_ = nullptr, *d_scale32_ = nullptr;
-    EvalParams *d_params_ = nullptr;
-    uint32_t *d_sub_first_ = nullptr, *d_head_ = nullptr;
+    uint32_t *d_sub_first_ = nullptr;
     WorkItem *d_items_ = nullptr;
     double *d_item_rec_ = nullptr, *d_item_split_ = nullptr, *d_sub_rec_ = nullptr,
            *d_sub_split_ = nullptr;
-    size_t cap_d_sub_[6] = {}, cap_d_map_[6] = {}, cap_d_items_[3] = {}, cap_dparams_ = 0,
-           cap_head_ = 0;
+    size_t cap_d_sub_[3] = {}, cap_d_map_[4] = {}, cap_d_items_[3] = {};
     hipGraphExec_t exec_ = nullptr;
     hipEvent_t ev_start_ = nullptr, ev_stop_ = nullptr;
     int instantiations_ = 0, updates_ = 0;

@@ -474,14 +474,11 @@ public:
         (void)hipStreamSynchronize(ctx_->stream);
         for (void *p : {static_cast<void *>(rec_), static_cast<void *>(split_),
                         static_cast<void *>(base_), static_cast<void *>(vol_),
-                        static_cast<void *>(e_d_), static_cast<void *>(gain_d_),
-                        static_cast<void *>(best_d_), static_cast<void *>(scratch_),
-                        static_cast<void *>(totals_d_), static_cast<void *>(fold_d_)})
+                        static_cast<void *>(out_d_), static_cast<void *>(scratch_),
+                        static_cast<void *>(fold_d_)})
             if (p)
                 (void)hipFree(p);
-        for (void *p : {static_cast<void *>(h_e_), static_cast<void *>(h_gain_),
-                        static_cast<void *>(h_best_), static_cast<void *>(h_totals_),
-                        static_cast<void *>(h_fold_)})
+        for (void *p : {static_cast<void *>(h_out_), static_cast<void *>(h_fold_)})
             if (p)
                 (void)hipHostFree(p);
         for (hipEvent_t ev : {ev_f0_, ev_f1_, ev_a0_, ev_e_, ev_a1_})
@@ -505,10 +502,6 @@ public:
         BFI_HIP(grow_keep(&split_, &c_split, leaves * split_len_, keep * split_len_, st));
         BFI_HIP(grow_keep(&base_, &c_base, leaves * rec_len_, keep * rec_len_, st));
         BFI_HIP(grow_keep(&vol_, &c_vol, leaves, keep, st));
-        size_t c_e = cap_, c_g = cap_, c_b = cap_;
-        BFI_HIP(grow_keep(&e_d_, &c_e, leaves, 0, st));
-        BFI_HIP(grow_keep(&gain_d_, &c_g, leaves, 0, st));
-        BFI_HIP(grow_keep(&best_d_, &c_b, leaves, 0, st));
         cap_ = leaves;
         return BFI_OK;
     }
@@ -553,32 +546,41 @@ public:
         BFI_HIP(grow_keep(&scratch_, &cap_scratch_,
                           analysis_scratch_doubles(static_cast<uint32_t>(count), nx_), 0, st));
         const size_t ntot = 1 + 4 + 2 * static_cast<size_t>(nx_);
-        BFI_HIP(grow_keep(&totals_d_, &cap_totals_, ntot, 0, st));
-        BFI_HIP(grow_pinned_buf(&h_totals_, &cap_htotals_, ntot));
-        BFI_HIP(grow_pinned_buf(&h_e_, &cap_he_, count));
-        BFI_HIP(grow_pinned_buf(&h_gain_, &cap_hg_, count));
-        BFI_HIP(grow_pinned_buf(&h_best_, &cap_hb_, count));
+        // one block each side, [totals | e | gain | best]: one copy for what the
+        // ranking reads, one for the choices
+        const size_t choices = ntot + count, doubles = choices + count + (count + 1) / 2;
+        BFI_HIP(grow_keep(&out_d_, &cap_dout_, doubles, 0, st));
+        BFI_HIP(grow_pinned_buf(&h_out_, &cap_hout_, doubles));
+        h_e_ = h_out_ + ntot;
+        h_gain_ = h_out_ + choices;
+        h_best_ = reinterpret_cast<int32_t *>(h_gain_ + count);
         BFI_HIP(hipEventRecord(ev_a0_, st));
-        LeafAnalysisArgs la{rec_,   split_,   base_,     vol_,   static_cast<uint32_t>(count),
-                            nx_,    d_,       scratch_,  totals_d_, e_d_,
-                            gain_d_, best_d_};
+        LeafAnalysisArgs la{rec_,
+                            split_,
+                            base_,
+                            vol_,
+                            static_cast<uint32_t>(count),
+                            nx_,
+                            d_,
+                            scratch_,
+                            out_d_,
+                            out_d_ + ntot,
+                            out_d_ + choices,
+                            reinterpret_cast<int32_t *>(out_d_ + choices + count)};
         BFI_HIP(launch_leaf_analysis(la, st));
-        BFI_HIP(hipMemcpyAsync(h_totals_, totals_d_, ntot * sizeof(double), hipMemcpyDeviceToHost,
-                               st));
-        BFI_HIP(hipMemcpyAsync(h_e_, e_d_, count * sizeof(double), hipMemcpyDeviceToHost, st));
+        BFI_HIP(hipMemcpyAsync(h_out_, out_d_, choices * sizeof(double), hipMemcpyDeviceToHost, st));
         BFI_HIP(hipEventRecord(ev_e_, st));
         // the split choices come back while the host ranks the leaves by e
         // (wait_choices before reading them)
-        BFI_HIP(hipMemcpyAsync(h_gain_, gain_d_, count * sizeof(double), hipMemcpyDeviceToHost, st));
-        BFI_HIP(hipMemcpyAsync(h_best_, best_d_, count * sizeof(int32_t), hipMemcpyDeviceToHost,
-                               st));
+        BFI_HIP(hipMemcpyAsync(h_out_ + choices, out_d_ + choices,
+                               (doubles - choices) * sizeof(double), hipMemcpyDeviceToHost, st));
         BFI_HIP(hipEventRecord(ev_a1_, st));
         choices_pending_ = true;
         BFI_HIP(hipEventSynchronize(ev_e_));
         // the estimate from the totals, as the finalize forms it
         std::memset(res, 0, sizeof(*res));
         res->nx = nx_;
-        const double *T = h_totals_;
+        const double *T = h_out_;
         const double sig = T[0], z = T[1];
         if (!std::isfinite(sig))
             return fail(BFI_EINVAL, "partial records carry no finite shift");
@@ -629,13 +631,13 @@ private:
     int nx_, d_, rec_len_, split_len_;
     size_t cap_ = 0;  // leaves
     double *rec_ = nullptr, *split_ = nullptr, *base_ = nullptr, *vol_ = nullptr;
-    double *e_d_ = nullptr, *gain_d_ = nullptr, *scratch_ = nullptr, *totals_d_ = nullptr;
-    int32_t *best_d_ = nullptr;
+    double *out_d_ = nullptr, *scratch_ = nullptr;
     FoldEntry *fold_d_ = nullptr, *h_fold_ = nullptr;
-    size_t cap_scratch_ = 0, cap_totals_ = 0, cap_dfold_ = 0, cap_hfold_ = 0;
-    double *h_e_ = nullptr, *h_gain_ = nullptr, *h_totals_ = nullptr;
+    size_t cap_scratch_ = 0, cap_dout_ = 0, cap_hout_ = 0, cap_dfold_ = 0, cap_hfold_ = 0;
+    double *h_out_ = nullptr;
+    // pieces of h_out_ for the last analysis's count
+    double *h_e_ = nullptr, *h_gain_ = nullptr;
     int32_t *h_best_ = nullptr;
-    size_t cap_he_ = 0, cap_hg_ = 0, cap_hb_ = 0, cap_htotals_ = 0;
     hipEvent_t ev_f0_ = nullptr, ev_f1_ = nullptr, ev_a0_ = nullptr, ev_e_ = nullptr,
                ev_a1_ = nullptr;
     bool choices_pending_ = false;

@@ -140,7 +140,9 @@ typedef struct {
                                    (split statistics: 256; the Gaussian-proposal
                                    and N-sphere samplers: 64, 128 or 256) */
     int32_t persistent;         /* 1: persistent kernel draining a device queue;
-                                   0: one block per work item; -1: tuned */
+                                   0: one block per work item; -1: tuned (short
+                                   lists take a block per item whatever the tuned
+                                   shape says: the records are the same) */
     int32_t use_graph;          /* 1: replay a captured hipGraph (plans only) */
 } bfi_launch;
 

@@ -201,7 +201,8 @@ extern "C" bfi_status bfi_eval_noalloc(bfi_context *ctx, const bfi_lattice *lat,
                      rec_len};
         BFI_HIP(launch_build_items(ba, st));
 
-        if (l.persistent) {
+        const bool queue = item_queue(l, launch, chunk, nitems, resident);
+        if (queue) {
             spec.grid = static_cast<uint32_t>(std::min<uint64_t>(resident, nitems));
             BFI_HIP(launch_reset_head(head, st));
         } else {
@@ -211,7 +212,7 @@ extern "C" bfi_status bfi_eval_noalloc(bfi_context *ctx, const bfi_lattice *lat,
         a.items = items;
         a.item_rec = item_rec;
         a.item_split = item_split;
-        a.queue_head = l.persistent ? head : nullptr;
+        a.queue_head = queue ? head : nullptr;
         a.nitems = static_cast<uint32_t>(nitems);
         a.samples_per_thread = static_cast<uint32_t>(l.samples_per_thread);
         BFI_HIP(launch_mc(lat->nx, lat->nt, spec, a, st));

@@ -293,8 +293,6 @@ uint64_t item_samples(const bfi_launch &l, bool spread, const uint64_t *n, size_
 {
     const uint64_t block = static_cast<uint64_t>(l.block);
     const uint64_t most = static_cast<uint64_t>(l.samples_per_thread) * block;
-    // the resident blocks' rounds of items from which the last one no longer matters
-    constexpr uint64_t kRounds = 8;
     if (!spread || resident == 0 || nsub > kRounds * resident)
         return most;
     uint64_t total = 0;
@@ -321,8 +319,11 @@ uint64_t item_samples(const bfi_launch &l, bool spread, const uint64_t *n, size_
         for (size_t s = 0; s < nsub; ++s)
             items += n[s] / chunk + (n[s] % chunk != 0);
         // two upper bounds of the time of blocks that take the next item as they
-        // go: whole rounds of the longest item, and the shared work plus one item
-        const uint64_t rounds = (items + resident - 1) / resident * (m + kItemCost);
+        // go: whole rounds of the longest item (and a sixteenth of one: the blocks
+        // do not run equally fast, so that few long rounds end unevenly), and the
+        // shared work plus one item
+        const uint64_t rounds =
+            (items + resident - 1) / resident * (m + kItemCost) + m / 16;
         const uint64_t shared =
             (total / block + items * kItemCost + resident - 1) / resident + m + kItemCost;
         const uint64_t cost = std::min(rounds, shared);
@@ -834,7 +835,8 @@ bfi_status plan_build_core(bfi_context *ctx, const PlanSpec &what, const bfi_sub
         BFI_HIP(hipEventCreate(&p->ev_stop));
     }
     // persistent launches fill the chip once
-    p->grid = static_cast<uint32_t>(l.persistent ? std::min<uint64_t>(resident, nitems) : nitems);
+    p->queue = item_queue(l, launch, chunk, nitems, resident);
+    p->grid = static_cast<uint32_t>(p->queue ? std::min<uint64_t>(resident, nitems) : nitems);
     guard.p = nullptr;
     *out = p;
     return BFI_OK;
@@ -931,13 +933,13 @@ bfi_status plan_enqueue(bfi_plan *p, uint64_t seed, double *dst, hipStream_t st,
     a.items = p->d_items;
     a.item_rec = p->d_item_rec;
     a.item_split = p->d_item_split;
-    a.queue_head = p->launch.persistent ? p->d_head : nullptr;
+    a.queue_head = p->queue ? p->d_head : nullptr;
     a.nitems = p->nitems;
     a.samples_per_thread = static_cast<uint32_t>(p->launch.samples_per_thread);
     LaunchSpec spec{p->prec,  p->launch.block,    p->split ? 1 : 0, p->launch.persistent,
                     p->grid,  p->lat.observable, p->lat.antithetic};
     // (a lent block's queue head came with its upload, and it runs once)
-    if (p->launch.persistent && p->d_block)
+    if (p->queue && p->d_block)
         BFI_HIP(launch_reset_head(p->d_head, st));
     if (timed)
         BFI_HIP(hipEventRecord(p->ev_start, st));

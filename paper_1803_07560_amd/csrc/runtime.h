@@ -159,11 +159,33 @@ inline bool spread_items(int prec, const bfi_launch *req)
 // Measured, launch shape's items -> these, whole calls: 10x2 FP64, 3e6
 // evaluations over 64 subvolumes 416 -> 291 us; 301 uneven leaves of 2^10 ..
 // 2^17 samples with split statistics 925 -> 501 us; spherical sampler, 2^24
-// over 64 shells in two passes 2.16 -> 1.60 ms.  From eight rounds on the
+// over 64 shells in two passes 2.16 -> 1.60 ms; 2^27 evaluations of 8x2 as pairs,
+// one round of 512 items -> four of a quarter of them, 1.04 -> 0.98 ms.  From
+// eight rounds on the
 // launch shape's items are as fast and there are fewer records to merge (2^30
 // evaluations of 10x2: the same 4096 items, 11.8 ms).
 uint64_t item_samples(const bfi_launch &l, bool spread, const uint64_t *n, size_t nsub,
                       uint64_t resident);
+
+// Rounds of items over the resident blocks from which a list counts as long: the
+// last round and the start no longer matter.
+constexpr uint64_t kRounds = 8;
+// Whether the items are drained through a queue or each has a block of its own
+// (the records are the same): as asked, or where the caller left it open, as the
+// launch shape has it for long lists and long items.  Every block's first item
+// and each short one costs the queue's counter 10 ns of its own, all blocks one
+// after another: 4x2 FP64, 1984 items of 6 samples per thread took 41 us through
+// the queue, 25 as blocks; 10x2, 1024 items of 12 samples 53 and 48; from 64
+// samples per thread on both are equal, and on the longest lists the queue is
+// ahead (2^30 of 10x2 FP64 11.74 ms, 11.84 as blocks).
+inline bool item_queue(const bfi_launch &l, const bfi_launch *req, uint64_t chunk, uint64_t nitems,
+                       uint64_t resident)
+{
+    if (!l.persistent || (req && req->persistent >= 0))
+        return l.persistent != 0;
+    const bool brief = chunk <= 64 * static_cast<uint64_t>(l.block);
+    return nitems >= kRounds * resident || (nitems > resident && !brief);
+}
 
 // Work items of a list: record slots in list order (sub_first: first slot of each
 // subvolume, nsub + 1 entries), the items themselves in the order in which blocks
@@ -328,6 +350,7 @@ struct bfi_plan {
     size_t nsub = 0;
     bfi_launch launch{};
     uint32_t nitems = 0, most_items = 0;  // of the list, and of its largest subvolume
+    bool queue = false;  // items through the queue (item_queue)
     bool fixed_order = false;  // one-wavefront merge: sums in the launch shape's order
     uint32_t grid = 0;
     uint64_t n_evals = 0;

@@ -159,11 +159,12 @@ bfi_status sph_eval(bfi_context *ctx, const bfi_lattice &lat, int prec, uint64_t
     BFI_TRY(scratch.upload(image));
 
     auto *head = reinterpret_cast<uint32_t *>(base + o_head);
-    spec.grid = static_cast<uint32_t>(l.persistent ? std::min<uint64_t>(resident, nitems) : nitems);
+    const bool queue = item_queue(l, launch, chunk, nitems, resident);
+    spec.grid = static_cast<uint32_t>(queue ? std::min<uint64_t>(resident, nitems) : nitems);
     SphArgs a{};
     a.mc.items = reinterpret_cast<const WorkItem *>(base + o_items);
     a.mc.item_split = nullptr;
-    a.mc.queue_head = l.persistent ? head : nullptr;
+    a.mc.queue_head = queue ? head : nullptr;
     a.mc.nitems = static_cast<uint32_t>(nitems);
     a.mc.samples_per_thread = static_cast<uint32_t>(l.samples_per_thread);
     a.shell64 = reinterpret_cast<const double *>(base + o_s64);

@@ -128,6 +128,8 @@ bfi_status ResidentEval::init(bfi_context *ctx, const bfi_lattice &lat, int prec
     split_len_ = BFI_SPLIT_LEN(d_);
     launch_ = resolve_launch(ctx, lat, prec, split, launch);
     launch_.use_graph = 1;
+    launch_.persistent = 1;
+    asked_ = launch && launch->persistent >= 0;
     if (!mc_block_ok(launch_.block))
         return fail(BFI_EINVAL, "block must be 64, 128, 256, 512 or 1024 (got %d)", launch_.block);
     if (launch_.samples_per_thread < 1 || launch_.samples_per_thread > (1 << 20))
@@ -303,14 +305,17 @@ bfi_status ResidentEval::enqueue(size_t nsub, uint64_t nitems, hipStream_t st)
                  d_scale64_, d_base32_, d_scale32_, d_items_, params, d_item_rec_, chunk_,
                  static_cast<uint32_t>(nsub), d_, rec_len_};
     BFI_HIP(launch_build_items(ba, st));
-    LaunchSpec spec{prec_, launch_.block, split_ ? 1 : 0, 1,
-                    static_cast<uint32_t>(std::min<uint64_t>(resident_blocks_, nitems)),
+    const bool queue =
+        asked_ || item_queue(launch_, nullptr, chunk_, nitems, resident_blocks_);
+    LaunchSpec spec{prec_, launch_.block, split_ ? 1 : 0, queue ? 1 : 0,
+                    static_cast<uint32_t>(
+                        queue ? std::min<uint64_t>(resident_blocks_, nitems) : nitems),
                     lat_.observable, lat_.antithetic};
     McArgs a{};
     a.items = d_items_;
     a.item_rec = d_item_rec_;
     a.item_split = split_ ? d_item_split_ : nullptr;
-    a.queue_head = reinterpret_cast<uint32_t *>(d_stage_ + at.head);
+    a.queue_head = queue ? reinterpret_cast<uint32_t *>(d_stage_ + at.head) : nullptr;
     a.nitems = static_cast<uint32_t>(nitems);
     a.samples_per_thread = static_cast<uint32_t>(launch_.samples_per_thread);
     BFI_HIP(launch_mc(lat_.nx, lat_.nt, spec, a, st));

@@ -578,7 +578,7 @@ bfi_status CallScratch::take(bfi_context *ctx, size_t host_bytes, size_t dev_byt
         ctx->scratch_host = nullptr;
         ctx->scratch_host_cap = 0;
         BFI_HIP(hipHostMalloc(reinterpret_cast<void **>(&ctx->scratch_host), cap,
-                              hipHostMallocDefault));
+                              hipHostMallocCoherent));
         ctx->scratch_host_cap = cap;
     }
     host_ = ctx->scratch_host;
@@ -596,6 +596,11 @@ bfi_status CallScratch::upload(size_t bytes)
 bfi_status CallScratch::download(size_t from, size_t bytes)
 {
     BFI_HIP(hipMemcpyAsync(host_, dev_ + from, bytes, hipMemcpyDeviceToHost, ctx_->stream));
+    return wait();
+}
+
+bfi_status CallScratch::wait()
+{
     BFI_HIP(hipStreamSynchronize(ctx_->stream));
     queued_ = false;
     return BFI_OK;
@@ -756,7 +761,8 @@ bfi_status plan_build_core(bfi_context *ctx, const PlanSpec &what, const bfi_sub
     } guard{p};
     char *img = nullptr, *dev = nullptr;
     if (scratch) {
-        BFI_TRY(scratch->take(ctx, std::max(image, records), at));
+        // (the image first, then room for the records of a direct merge)
+        BFI_TRY(scratch->take(ctx, image + records, at));
         img = scratch->host();
         dev = scratch->dev();
     } else {
@@ -784,10 +790,12 @@ bfi_status plan_build_core(bfi_context *ctx, const PlanSpec &what, const bfi_sub
     p->d_is_table = kind == 2 ? reinterpret_cast<IsTable *>(dev + o_table) : nullptr;
     p->d_items = reinterpret_cast<WorkItem *>(dev + o_items);
     p->d_sub_first = reinterpret_cast<uint32_t *>(dev + o_first);
-    p->d_sub_rec = reinterpret_cast<double *>(dev + o_sub_rec);
+    p->direct = scratch && scratch->direct(records);
+    char *const results = p->direct ? img : dev;
+    p->d_sub_rec = reinterpret_cast<double *>(results + o_sub_rec);
     p->d_item_rec = reinterpret_cast<double *>(dev + o_item_rec);
     if (split) {
-        p->d_sub_split = reinterpret_cast<double *>(dev + o_sub_split);
+        p->d_sub_split = reinterpret_cast<double *>(results + o_sub_split);
         p->d_item_split = reinterpret_cast<double *>(dev + o_item_split);
     }
     p->params.ids = reinterpret_cast<const uint64_t *>(dev + o_ids);
@@ -852,18 +860,24 @@ bfi_status run_once(bfi_context *ctx, const PlanSpec &what, const bfi_subvolumes
         BFI_TRY(plan_build_core(ctx, what, subs, &scratch, &p));
     }
     const size_t rec_bytes = p->nsub * p->rec_len * sizeof(double);
-    const size_t from = static_cast<size_t>(reinterpret_cast<char *>(p->d_sub_rec) - scratch.dev());
     const size_t split_bytes = split ? p->nsub * BFI_SPLIT_LEN(p->d) * sizeof(double) : 0;
+    const char *rec = reinterpret_cast<const char *>(p->d_sub_rec);
     const size_t split_at =
-        split ? static_cast<size_t>(reinterpret_cast<char *>(p->d_sub_split) - scratch.dev()) - from
-              : 0;
+        split ? static_cast<size_t>(reinterpret_cast<const char *>(p->d_sub_split) - rec) : 0;
+    const size_t bytes = split ? split_at + split_bytes : rec_bytes;
+    const bool direct = p->direct;
     bfi_status s = plan_enqueue(p, what.seed, nullptr, ctx->stream, false);
     plan_free(p);
     BFI_TRY(s);
-    BFI_TRY(scratch.download(from, split ? split_at + split_bytes : rec_bytes));
-    std::memcpy(partials, scratch.host(), rec_bytes);
+    if (direct) {
+        BFI_TRY(scratch.wait());
+    } else {
+        BFI_TRY(scratch.download(static_cast<size_t>(rec - scratch.dev()), bytes));
+        rec = scratch.host();
+    }
+    std::memcpy(partials, rec, rec_bytes);
     if (split)
-        std::memcpy(split, scratch.host() + split_at, split_bytes);
+        std::memcpy(split, rec + split_at, split_bytes);
     return BFI_OK;
 }
 

@@ -285,6 +285,7 @@ private:
     bfi_lattice lat_{};
     int prec_ = 0, d_ = 0, rec_len_ = 0, split_len_ = 0;
     bool split_ = false, copy_records_ = true;
+    bool asked_ = false;  // the caller chose the queue (else item_queue does)
     bfi_launch launch_{};
     uint64_t chunk_ = 0, resident_blocks_ = 0;
     size_t count_ = 0;
@@ -350,6 +351,7 @@ struct bfi_plan {
     size_t nsub = 0;
     bfi_launch launch{};
     uint32_t nitems = 0, most_items = 0;  // of the list, and of its largest subvolume
+    bool direct = false;  // d_sub_rec, d_sub_split in the call's pinned block
     bool queue = false;  // items through the queue (item_queue)
     bool fixed_order = false;  // one-wavefront merge: sums in the launch shape's order
     uint32_t grid = 0;
@@ -404,11 +406,18 @@ public:
     bfi_status take(bfi_context *ctx, size_t host_bytes, size_t dev_bytes);
     char *host() const { return host_; }
     char *dev() const { return dev_; }
+    // Whether kernels may write `bytes` of results straight into the host block
+    // (pinned, the context's own): up to 64 KiB, which the bus takes within the
+    // merge's own time.  A copy apart cost a call 4 us (2^16 evaluations of 4x2: 44
+    // -> @D@ us).
+    bool direct(size_t bytes) const { return held_.owns_lock() && bytes <= (size_t(64) << 10); }
     // copy the first `bytes` of the host block to the device block
     bfi_status upload(size_t bytes);
     // copy `bytes` of the device block from `from` to the host block's start and
     // wait for them
     bfi_status download(size_t from, size_t bytes);
+    // wait for what is queued
+    bfi_status wait();
 
 private:
     bfi_context *ctx_ = nullptr;

@@ -133,7 +133,8 @@ bfi_status sph_eval(bfi_context *ctx, const bfi_lattice &lat, int prec, uint64_t
                  image = at, o_srec = take(ns * rec_len * 8), o_irec = take(nitems * rec_len * 8);
     const size_t rec_bytes = ns * rec_len * 8;
     CallScratch scratch;
-    BFI_TRY(scratch.take(ctx, std::max(image, rec_bytes), at));
+    // (the image first, then room for the records of a direct merge)
+    BFI_TRY(scratch.take(ctx, image + rec_bytes, at));
     char *base = scratch.dev(), *img = scratch.host();
     auto *params = reinterpret_cast<EvalParams *>(base + o_params);
     const EvalParams P{nullptr, nullptr, nullptr, nullptr,
@@ -175,15 +176,19 @@ bfi_status sph_eval(bfi_context *ctx, const bfi_lattice &lat, int prec, uint64_t
     MergeArgs m{};
     m.item_rec = reinterpret_cast<const double *>(base + o_irec);
     m.sub_first = reinterpret_cast<const uint32_t *>(base + o_first);
-    m.sub_rec = reinterpret_cast<double *>(base + o_srec);
+    const bool direct = scratch.direct(rec_bytes);
+    m.sub_rec = reinterpret_cast<double *>((direct ? img : base) + o_srec);
     m.nsub = static_cast<uint32_t>(ns);
     m.nitems = static_cast<uint32_t>(nitems);
     m.most = static_cast<uint32_t>(most);
     m.nx = lat.nx;
     m.d = d;
     BFI_HIP(launch_merge(m, st));
-    BFI_TRY(scratch.download(o_srec, rec_bytes));
-    std::memcpy(partials, scratch.host(), rec_bytes);
+    if (direct)
+        BFI_TRY(scratch.wait());
+    else
+        BFI_TRY(scratch.download(o_srec, rec_bytes));
+    std::memcpy(partials, direct ? img + o_srec : scratch.host(), rec_bytes);
     return BFI_OK;
 }
 

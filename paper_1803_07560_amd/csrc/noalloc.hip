@@ -146,7 +146,7 @@ extern "C" bfi_status bfi_eval_noalloc(bfi_context *ctx, const bfi_lattice *lat,
         uint64_t chunk = 0, nitems = 0, most = 0;
         Layout L{};
         for (;;) {
-            chunk = item_samples(l, spread, subs->n, nsub, resident);
+            chunk = item_samples(l, spread, split != nullptr, subs->n, nsub, resident);
             nitems = most = 0;
             for (size_t s = 0; s < nsub; ++s) {
                 const uint64_t count = subs->n[s] / chunk + (subs->n[s] % chunk != 0);

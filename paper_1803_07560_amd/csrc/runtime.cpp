@@ -288,7 +288,7 @@ bfi_launch resolve_launch(const bfi_context *ctx, const bfi_lattice &lat, int pr
     return l;
 }
 
-uint64_t item_samples(const bfi_launch &l, bool spread, const uint64_t *n, size_t nsub,
+uint64_t item_samples(const bfi_launch &l, bool spread, bool split, const uint64_t *n, size_t nsub,
                       uint64_t resident)
 {
     const uint64_t block = static_cast<uint64_t>(l.block);
@@ -303,9 +303,9 @@ uint64_t item_samples(const bfi_launch &l, bool spread, const uint64_t *n, size_
     }
     if (total >= kRounds * resident * most)
         return most;
-    // in samples per thread: what an item costs beside its samples (the queue,
-    // its parameters, the reduction)
-    constexpr uint64_t kItemCost = 3;
+    // in samples per thread: what an item costs beside its samples (its
+    // parameters, the reduction; with split statistics of twice the sums)
+    const uint64_t item_cost = split ? 6 : 3;
     uint64_t best = most, best_cost = ~uint64_t(0), last = 0;
     for (uint64_t k : {1, 2, 3, 4, 6, 8}) {
         const uint64_t m = std::min<uint64_t>((total + k * resident * block - 1) /
@@ -318,14 +318,14 @@ uint64_t item_samples(const bfi_launch &l, bool spread, const uint64_t *n, size_
         uint64_t items = 0;
         for (size_t s = 0; s < nsub; ++s)
             items += n[s] / chunk + (n[s] % chunk != 0);
-        // two upper bounds of the time of blocks that take the next item as they
-        // go: whole rounds of the longest item (and a sixteenth of one: the blocks
-        // do not run equally fast, so that few long rounds end unevenly), and the
-        // shared work plus one item
+        // two estimates of the time of blocks that take the next item as they go,
+        // the longest first: whole rounds of the longest item (and a sixteenth of
+        // one: the blocks do not run equally fast, so that few long rounds end
+        // unevenly), and the shared work plus a short item
         const uint64_t rounds =
-            (items + resident - 1) / resident * (m + kItemCost) + m / 16;
+            (items + resident - 1) / resident * (m + item_cost) + m / 16;
         const uint64_t shared =
-            (total / block + items * kItemCost + resident - 1) / resident + m + kItemCost;
+            (total / block + items * item_cost + resident - 1) / resident + m / 4 + item_cost;
         const uint64_t cost = std::min(rounds, shared);
         if (cost < best_cost) {
             best_cost = cost;
@@ -709,8 +709,8 @@ bfi_status plan_build_core(bfi_context *ctx, const PlanSpec &what, const bfi_sub
                             &resident));
 
     // work items: ceil(n / chunk) per subvolume, subvolumes in list order
-    const uint64_t chunk = item_samples(l, spread_items(prec, launch) && !what.fixed_order, subs.n,
-                                        nsub, resident);
+    const uint64_t chunk = item_samples(l, spread_items(prec, launch) && !what.fixed_order, split,
+                                        subs.n, nsub, resident);
     uint64_t nitems = 0, most = 0, n_evals = 0;
     for (size_t s = 0; s < nsub; ++s) {
         // checked per subvolume, so the running count cannot wrap

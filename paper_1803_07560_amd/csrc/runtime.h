@@ -155,7 +155,7 @@ inline bool spread_items(int prec, const bfi_launch *req)
 // items over the `resident` blocks leaves blocks without work (2^6 subvolumes
 // of 46875 samples made 64 items for 512 blocks) and ends on a round that is
 // partly empty.  With `spread`, such a list is cut into about one to eight
-// rounds of shorter items, as many as a bound of the finishing time prefers.
+// rounds of shorter items, as many as an estimate of the finishing time prefers.
 // Measured, launch shape's items -> these, whole calls: 10x2 FP64, 3e6
 // evaluations over 64 subvolumes 416 -> 291 us; 301 uneven leaves of 2^10 ..
 // 2^17 samples with split statistics 925 -> 501 us; spherical sampler, 2^24
@@ -164,7 +164,7 @@ inline bool spread_items(int prec, const bfi_launch *req)
 // eight rounds on the
 // launch shape's items are as fast and there are fewer records to merge (2^30
 // evaluations of 10x2: the same 4096 items, 11.8 ms).
-uint64_t item_samples(const bfi_launch &l, bool spread, const uint64_t *n, size_t nsub,
+uint64_t item_samples(const bfi_launch &l, bool spread, bool split, const uint64_t *n, size_t nsub,
                       uint64_t resident);
 
 // Rounds of items over the resident blocks from which a list counts as long: the
@@ -408,8 +408,8 @@ public:
     char *dev() const { return dev_; }
     // Whether kernels may write `bytes` of results straight into the host block
     // (pinned, the context's own): up to 64 KiB, which the bus takes within the
-    // merge's own time.  A copy apart cost a call 4 us (2^16 evaluations of 4x2: 44
-    // -> @D@ us).
+    // merge's own time.  A copy apart cost a call 2 to 7 us (2^16 evaluations of
+    // 4x2 44 us with it, 42 without; 3e6 of 10x2 92 and 85).
     bool direct(size_t bytes) const { return held_.owns_lock() && bytes <= (size_t(64) << 10); }
     // copy the first `bytes` of the host block to the device block
     bfi_status upload(size_t bytes);

@@ -108,7 +108,7 @@ bfi_status sph_eval(bfi_context *ctx, const bfi_lattice &lat, int prec, uint64_t
     LaunchSpec spec{prec, l.block, 0, l.persistent, 0, lat.observable, 0};
     uint64_t resident = 0;
     BFI_TRY(resident_blocks(ctx, 3, lat, spec, &resident));
-    const uint64_t chunk = item_samples(l, spread_items(prec, launch), sh.n, ns, resident);
+    const uint64_t chunk = item_samples(l, spread_items(prec, launch), false, sh.n, ns, resident);
     uint64_t nitems = 0, most = 0;
     for (size_t s = 0; s < ns; ++s) {
         const uint64_t count = sh.n[s] / chunk + (sh.n[s] % chunk != 0);

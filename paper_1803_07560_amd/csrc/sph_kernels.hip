@@ -89,8 +89,17 @@ __device__ __forceinline__ void shell_point(const dev::PhiloxStream &words, uint
         u[k] *= f;
 }
 
+// FP64 takes about 9 registers a site and a third wave of a SIMD ends at 168:
+// up to 16 sites fit by themselves, 20 sites need 181 and are held at 168 for
+// 28 bytes of scratch (10x2, 2^24 samples, 590 -> 582 us over one shell and
+// 2035 -> 1960 over 26; 8x2 with the same bound 877 -> 888,
+// another schedule of the same registers); 24 sites would spill 136 bytes.
+template <int SITES, int PREC>
+constexpr int kSphWaves = PREC == kFP64 && SITES > 16 && SITES <= 20 ? 3 : 1;
+
 template <int NX, int NT, int PREC, int BLOCK, bool AVG>
-__global__ void __launch_bounds__(BLOCK) sph_kernel(SphArgs sa)
+__global__ void __launch_bounds__(BLOCK)
+    __attribute__((amdgpu_waves_per_eu(kSphWaves<NX * NT, PREC>))) sph_kernel(SphArgs sa)
 {
     using T = std::conditional_t<PREC == kFP64, double, float>;
     constexpr int D = NX * NT;

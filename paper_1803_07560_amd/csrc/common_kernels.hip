@@ -229,7 +229,8 @@ __device__ __forceinline__ double sqrt_unit(double a)
 // computed once.  What bounds it is instruction issue.  A kernel for any
 // dimension up to 16 kept 34 sums whatever the dimension, read the map from
 // memory for every coordinate and masked the unused ones: a call of 3.2e7
-// samples in 6 dimensions took 338 us with it, 201 us with this.
+// samples in 6 dimensions took 338 us with it, 201 us with this (161 with the
+// shorter items, block launch and merge batches of today).
 template <int DIM>
 __global__ void __launch_bounds__(256) nsphere_kernel(McArgs a)
 {

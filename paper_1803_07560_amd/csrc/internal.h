@@ -218,6 +218,8 @@ hipError_t nsphere_kernel_info(int dim, KernelInfo *info);
 hipError_t launch_build_items(const BuildArgs &args, hipStream_t stream);
 hipError_t launch_reset_head(uint32_t *head, hipStream_t stream);
 hipError_t launch_merge(const MergeArgs &args, hipStream_t stream);
+// The same for n lists, as few launches as their sizes allow.
+hipError_t launch_merges(const MergeArgs *args, size_t n, hipStream_t stream);
 hipError_t launch_debug_points(const DebugPointArgs &args, hipStream_t stream);
 
 }  // namespace bfi

@@ -124,6 +124,8 @@ struct bfi_server {
     uint64_t used_bytes = 0;
     bfi_server_stats stats{};
     static constexpr int kStreams = 4;
+    // records that a merge writes over the bus within its own time
+    static constexpr size_t kDirectBytes = size_t(64) << 10;
     hipStream_t stream = nullptr;              // copies, merges, first group
     hipStream_t group_streams[kStreams] = {};  // group g runs on group_streams[g % 4]
     hipEvent_t staged = nullptr;               // step items copied to the device
@@ -317,8 +319,9 @@ void admit(bfi_server *srv)
 }
 
 // Merge and finalize requests whose items are all done; release cancelled ones.
-// Every finished request's merge and record copy is enqueued first, then one
-// wait covers them all.
+// All finished requests merge in one launch (or a few, by size), which writes
+// records of up to kDirectBytes to the pinned block itself; longer ones are
+// copied.  One wait covers them all.
 void complete(bfi_server *srv)
 {
     std::vector<uint64_t> keep;
@@ -343,13 +346,13 @@ void complete(bfi_server *srv)
     TraceRange trace("server: merge and finalize finished requests");
     hipError_t e = grow_pinned(&srv->h_done, &srv->done_cap, bytes);
     std::vector<double *> host(ready.size());
+    std::vector<MergeArgs> merges(ready.size());
     size_t at = 0;
-    for (size_t i = 0; i < ready.size() && e == hipSuccess; ++i) {
+    for (size_t i = 0; i < ready.size(); ++i) {
         Request *r = ready[i];
-        MergeArgs m{};
+        MergeArgs &m = merges[i];
         m.item_rec = r->d_item_rec;
         m.sub_first = r->d_sub_first;
-        m.sub_rec = r->d_sub_rec;
         m.nsub = static_cast<uint32_t>(r->subs.size());
         m.nitems = static_cast<uint32_t>(r->items.size());
         for (size_t k = 0; k < r->subs.size(); ++k)
@@ -359,12 +362,18 @@ void complete(bfi_server *srv)
         host[i] = reinterpret_cast<double *>(srv->h_done + at);
         const size_t n = r->subs.size() * r->rec_len * sizeof(double);
         at += n;
-        e = launch_merge(m, srv->stream);
-        if (e == hipSuccess)
-            e = hipMemcpyAsync(host[i], r->d_sub_rec, n, hipMemcpyDeviceToHost, srv->stream);
+        m.sub_rec = n <= bfi_server::kDirectBytes ? host[i] : r->d_sub_rec;
     }
     if (e == hipSuccess)
-        e = hipStreamSynchronize(srv->stream);
+        e = launch_merges(merges.data(), merges.size(), srv->stream);
+    for (size_t i = 0; i < ready.size() && e == hipSuccess; ++i)
+        if (merges[i].sub_rec != host[i])
+            e = hipMemcpyAsync(host[i], merges[i].sub_rec,
+                               ready[i]->subs.size() * ready[i]->rec_len * sizeof(double),
+                               hipMemcpyDeviceToHost, srv->stream);
+    // (also after an error: what was launched reads the requests' blocks)
+    const hipError_t waited = hipStreamSynchronize(srv->stream);
+    e = e == hipSuccess ? waited : e;
     if (e != hipSuccess) {
         for (Request *r : ready)
             finish(srv, r, State::Failed, BFI_EDEVICE, hipGetErrorString(e));

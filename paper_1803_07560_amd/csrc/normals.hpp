@@ -14,23 +14,26 @@ namespace bfi {
 namespace dev {
 
 // The tables of the double-precision functions, copied to LDS once per block: a
-// lane's two reads per pair of normals are 16 bytes each at an address of its
-// own, which LDS serves beside the vector instructions.  With the library's log,
-// sincospi, pow, exp and log1p in their place (and the whole of Philox for every
-// block) 2^24 evaluations of 10x2 by the spherical sampler in FP64, pilot and
-// main pass, took 1.50 ms; with these 0.70 ms.  The errors of Z, C(r) and their
-// error bars against 64-bit sums over 80 inputs are those of before (medians
-// 1e-16 .. 2e-15).
+// lane's reads per pair of normals are 16, 16 and 4 bytes at addresses of its own,
+// which LDS serves beside the vector instructions.  What bounds the samplers is
+// instruction issue, in these functions above all.  2^24 evaluations of 10x2 in
+// FP64: spherical sampler, pilot and main pass, 0.63 ms; Gaussian proposal, 64
+// streams, 0.72 ms.  With the library's log, sincospi, pow, exp and log1p in their
+// place (and the whole of Philox for every block) they took 1.50 and 1.74 ms; with
+// shorter forms of up to twice the library's errors, 0.59 and 0.69 ms.
 struct NormalTables {
-    alignas(16) double log[64][2];
-    alignas(16) double turn[64][2];
+    alignas(16) double log[128][2];
+    alignas(16) nrm::TurnTable turn;
     __device__ __forceinline__ void load(uint32_t tid, uint32_t block)
     {
-        for (uint32_t i = tid; i < 64; i += block) {
+        for (uint32_t i = tid; i < 128; i += block) {
             log[i][0] = nrm::kLog[i][0];
             log[i][1] = nrm::kLog[i][1];
-            turn[i][0] = nrm::kTurn[i][0];
-            turn[i][1] = nrm::kTurn[i][1];
+        }
+        for (uint32_t i = tid; i < 64; i += block) {
+            turn.row[i][0] = nrm::kTurn.row[i][0];
+            turn.row[i][1] = nrm::kTurn.row[i][1];
+            turn.from[i] = nrm::kTurn.from[i];
         }
     }
 };

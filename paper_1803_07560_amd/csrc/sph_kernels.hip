@@ -66,8 +66,7 @@ __device__ __forceinline__ void shell_point(const dev::PhiloxStream &words, uint
     const uint32_t xr = blk[w & 3];
     T f;
     if constexpr (std::is_same_v<T, double>) {
-        // rho = rho_hi y^(1/D), as exp(ln y / D) from D = 3 on (the logarithm's
-        // error is divided by D)
+        // rho = rho_hi y^(1/D)
         const double v = __fma_rn(static_cast<double>(xr), 0x1p-32, 0x1p-33);
         const double y = __fma_rn(v, 1.0 - t, t);
         double rho;
@@ -76,8 +75,8 @@ __device__ __forceinline__ void shell_point(const dev::PhiloxStream &words, uint
         else if constexpr (D == 2)
             rho = rho_hi * nrm::root(y, __builtin_amdgcn_rsq(y));
         else
-            rho = rho_hi * exp_weight<dev::FmaSgprCoef>(nrm::minus_2log<0>(y, tab.log) * (-0.5 / D));
-        f = rho * nrm::reciprocal_root(norm2, __builtin_amdgcn_rsq(norm2));
+            rho = rho_hi * nrm::root_of_degree<D, dev::FmaSgprCoef>(y, tab.log);
+        f = nrm::over_root(rho, norm2, __builtin_amdgcn_rsq(norm2));
     } else {
         const float v = __fmaf_rn(static_cast<float>(xr), 0x1p-32f, 0x1p-33f);
         const float y = __fmaf_rn(v, 1.0f - t, t);

@@ -130,10 +130,17 @@ typedef struct {
 /* Launch shape.  A NULL bfi_launch* takes the tuned (else default) shape for
  * the lattice and precision; in a given struct, samples_per_thread = 0,
  * block = 0 and persistent = -1 each take the tuned value.  Work items hold
- * samples_per_thread * block consecutive samples of one subvolume; where the
+ * samples_per_thread * block consecutive samples of one subvolume, and a
+ * subvolume's record and split statistics depend on its own samples and that
+ * shape alone, not on the rest of the list or the chip.  One exception: where the
  * caller leaves samples_per_thread open, BFI_FP64 evaluations too small to fill
- * the chip with such items are cut into smaller ones (the sums differ from the
- * launch shape's in the order of summation only). */
+ * the chip with such items are cut into smaller ones, whose size follows the
+ * whole list and the chip (its CUs and the kernel's occupancy).  Then the sums
+ * differ from the launch shape's in the order of summation, that is in their last
+ * bits; a decision by split statistics (bfi_adaptive_decide) can hang on those
+ * where two dimensions tie, so a caller that compares decisions from list to list
+ * or from chip to chip gives samples_per_thread.  (The integrand calls and
+ * bfi_integrate_adaptive keep the launch shape's items by themselves.) */
 typedef struct {
     int32_t samples_per_thread; /* K: samples each thread takes per work item */
     int32_t block;              /* threads per block: 64, 128, 256, 512 or 1024

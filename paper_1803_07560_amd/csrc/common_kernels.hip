@@ -1,6 +1,7 @@
 // Shape-independent kernels: work items and point maps built on the device, queue
 // reset, the ordered per-subvolume merge of work-item records, and the
 // point-emitting test hook.
+#include <algorithm>
 #include <type_traits>
 
 #include "bfi.h"
@@ -74,22 +75,29 @@ __global__ void reset_head_kernel(uint32_t *head)
         *head = 0u;
 }
 
-// One block per subvolume: its items in GROUPS consecutive runs, a wavefront
-// each; thread f of a wavefront merges field f over its run in item order with
-// Neumaier compensation, after moving every item to the smallest shift of the
-// subvolume (factor exp(sigma_min - sigma_item) for first-order sums, its square
-// for second-order sums; 1 in FP64 form); the runs' sums and compensations then
-// merge in order.  Items are read kMergeBatch at a time, all loads of a batch
-// issued before its arithmetic (the sums keep item order).  What bounds it is
-// latency: a wavefront takes about a microsecond per batch, so the work items
-// per subvolume decide how many share them (launch_merge).  Measured, whole
-// calls: spherical sampler, 2^24 over 64 shells of up to some thousand items,
-// one wavefront and batches of 8 695 us, by the rule 623 us, batches of 16 601
-// us; 301 uneven leaves with split statistics 250 -> 237 us by the longer
-// batches.
+// One block per subvolume: its items in consecutive runs, as many as their number
+// says (merge_runs) and no matter what is merged beside them, so that a
+// subvolume's record does not depend on the rest of its list.  Thread f of a
+// wavefront merges field f over a run in item order with Neumaier compensation,
+// after moving every item to the smallest shift of the subvolume (factor
+// exp(sigma_min - sigma_item) for first-order sums, its square for second-order
+// sums; 1 in FP64 form); the runs' sums and compensations then merge in order.
+// Items are read kMergeBatch at a time, all loads of a batch issued before its
+// arithmetic (the sums keep item order).  What bounds it is latency: a wavefront
+// takes about a microsecond per batch, so the wavefronts of a block share the
+// runs (launch_merge).  Measured, whole calls: spherical sampler, 2^24 over 64
+// shells of up to some thousand items, one wavefront and batches of 8 695 us, by
+// the rule 623 us, batches of 16 601 us; 301 uneven leaves with split statistics
+// 250 -> 237 us by the longer batches.
 constexpr uint32_t kMergeBatch = 16;
-// (one wavefront for long runs: MergeArgs with nitems and most 0)
 constexpr int kMergeMaxFields = BFI_PARTIAL_LEN(BFI_MAX_NX) + 2 * 32;
+
+// One run for a batch of items, four for up to four batches, else sixteen.
+__host__ __device__ inline uint32_t merge_runs(uint64_t items)
+{
+    const uint64_t batches = (items + kMergeBatch - 1) / kMergeBatch;
+    return batches <= 1 ? 1 : batches <= 4 ? 4 : 16;
+}
 
 struct Compensated {
     double sum = 0.0, comp = 0.0;
@@ -101,12 +109,12 @@ struct Compensated {
     }
 };
 
-template <int GROUPS>
+template <int WAVES>
 __device__ __forceinline__ void merge_subvolume(const MergeArgs &m, uint32_t s)
 {
-    __shared__ double part[GROUPS > 1 ? GROUPS : 1][GROUPS > 1 ? kMergeMaxFields : 1][2];
-    __shared__ double low[GROUPS];
-    const uint32_t lane = threadIdx.x & 63u, group = threadIdx.x >> 6;
+    extern __shared__ double part[];  // runs x fields x (sum, compensation)
+    __shared__ double low[WAVES];
+    const uint32_t lane = threadIdx.x & 63u, wave = threadIdx.x >> 6;
     const int nx = m.nx, d = m.d;
     const int rec_len = 4 + 3 * nx;
     const int fields = rec_len + (m.item_split ? 2 * d : 0);
@@ -114,23 +122,21 @@ __device__ __forceinline__ void merge_subvolume(const MergeArgs &m, uint32_t s)
 
     // the smallest shift: items over the threads
     double sigma = __builtin_inf();
-    for (uint32_t i = i0 + threadIdx.x; i < i1; i += 64 * GROUPS)
+    for (uint32_t i = i0 + threadIdx.x; i < i1; i += 64 * WAVES)
         sigma = fmin(sigma, m.item_rec[static_cast<size_t>(i) * rec_len + 1]);
     sigma = dev::wave_min(sigma);
-    if constexpr (GROUPS > 1) {
+    if constexpr (WAVES > 1) {
         if (lane == 0)
-            low[group] = sigma;
+            low[wave] = sigma;
         __syncthreads();
 #pragma unroll
-        for (int g = 0; g < GROUPS; ++g)
+        for (int g = 0; g < WAVES; ++g)
             sigma = fmin(sigma, low[g]);
     }
     if (i0 == i1)
         sigma = 0.0;
 
-    const uint32_t per = (i1 - i0 + GROUPS - 1) / GROUPS;
-    const uint32_t a = i0 + group * per < i1 ? i0 + group * per : i1;
-    const uint32_t b = a + per < i1 ? a + per : i1;
+    const uint32_t runs = m.most ? merge_runs(i1 - i0) : 1, per = (i1 - i0 + runs - 1) / runs;
     double *out = m.sub_rec + static_cast<size_t>(s) * rec_len;
     auto store = [&](int f, const Compensated &c) {
         if (f < rec_len)
@@ -138,14 +144,20 @@ __device__ __forceinline__ void merge_subvolume(const MergeArgs &m, uint32_t s)
         else
             m.sub_split[static_cast<size_t>(s) * (1 + 2 * d) + 1 + (f - rec_len)] = c.sum + c.comp;
     };
-    for (int f = static_cast<int>(lane); f < fields; f += 64) {
-        if (f == 1)
+    // tasks: a run of 64 fields each, the runs of the same fields next to each other
+    Compensated total;  // one wavefront: over the runs of its fields
+    for (uint32_t task = wave; task < runs * ((fields + 63) / 64); task += WAVES) {
+        const uint32_t run = task % runs;
+        const int f = static_cast<int>(task / runs * 64 + lane);
+        if (f >= fields || f == 1)
             continue;
         int order;
         if (f < rec_len)
             order = f == 0 ? 0 : f == 2 ? 1 : f == 3 ? 2 : f < 4 + nx ? 1 : 2;
         else
             order = (f - rec_len) < d ? 1 : 2;
+        const uint32_t a = i0 + run * per < i1 ? i0 + run * per : i1;
+        const uint32_t b = i1 - a < per ? i1 : a + per;
         Compensated c;
         for (uint32_t i = a; i < b; i += kMergeBatch) {
             double vb[kMergeBatch], sb[kMergeBatch];
@@ -172,23 +184,32 @@ __device__ __forceinline__ void merge_subvolume(const MergeArgs &m, uint32_t s)
                 }
             }
         }
-        if constexpr (GROUPS > 1) {
-            part[group][f][0] = c.sum;
-            part[group][f][1] = c.comp;
-        } else {
+        if (runs == 1) {
             store(f, c);
+        } else if constexpr (WAVES > 1) {
+            double *p = part + (static_cast<size_t>(run) * fields + f) * 2;
+            p[0] = c.sum;
+            p[1] = c.comp;
+        } else {
+            if (run == 0)
+                total = Compensated();
+            total.add(c.sum);
+            total.add(c.comp);
+            if (run + 1 == runs)
+                store(f, total);
         }
     }
-    if constexpr (GROUPS > 1) {
+    if (WAVES > 1 && runs > 1) {
         __syncthreads();
-        for (int f = static_cast<int>(threadIdx.x); f < fields; f += 64 * GROUPS) {
+        for (int f = static_cast<int>(threadIdx.x); f < fields; f += 64 * WAVES) {
             if (f == 1)
                 continue;
             Compensated c;
-#pragma unroll
-            for (int g = 0; g < GROUPS; ++g) {
-                c.add(part[g][f][0]);
-                c.add(part[g][f][1]);
+#pragma unroll 4
+            for (uint32_t run = 0; run < runs; ++run) {
+                const double *p = part + (static_cast<size_t>(run) * fields + f) * 2;
+                c.add(p[0]);
+                c.add(p[1]);
             }
             store(f, c);
         }
@@ -200,10 +221,10 @@ __device__ __forceinline__ void merge_subvolume(const MergeArgs &m, uint32_t s)
     }
 }
 
-template <int GROUPS>
-__global__ void __launch_bounds__(64 * GROUPS) merge_kernel(MergeArgs m)
+template <int WAVES>
+__global__ void __launch_bounds__(64 * WAVES) merge_kernel(MergeArgs m)
 {
-    merge_subvolume<GROUPS>(m, blockIdx.x);
+    merge_subvolume<WAVES>(m, blockIdx.x);
 }
 
 // Several lists in one launch, their arguments in the kernel's own: list r's
@@ -218,13 +239,13 @@ struct MergeLists {
     uint32_t n;
 };
 
-template <int GROUPS>
-__global__ void __launch_bounds__(64 * GROUPS) merge_lists_kernel(MergeLists l)
+template <int WAVES>
+__global__ void __launch_bounds__(64 * WAVES) merge_lists_kernel(MergeLists l)
 {
     uint32_t r = 0;
     while (r + 1 < l.n && blockIdx.x >= l.first[r + 1])
         ++r;
-    merge_subvolume<GROUPS>(l.list[r], blockIdx.x - l.first[r]);
+    merge_subvolume<WAVES>(l.list[r], blockIdx.x - l.first[r]);
 }
 
 // The N-sphere integrand of the paper's examples (section 3, Listings 1 and 2):
@@ -460,22 +481,29 @@ hipError_t nsphere_kernel_info(int dim, KernelInfo *info)
 
 namespace {
 
-bool merge_fits(const MergeArgs &args)
+int merge_fields(const MergeArgs &args)
 {
-    return 4 + 3 * args.nx + (args.item_split ? 2 * args.d : 0) <= kMergeMaxFields;
+    return 4 + 3 * args.nx + (args.item_split ? 2 * args.d : 0);
 }
 
 // Wavefronts per subvolume: one for one batch of items, four for up to four,
 // else sixteen.  The largest subvolume decides while the blocks fit the chip
 // together (2048 of up to 16 wavefronts are four rounds); of longer lists the
-// average does, whose few large subvolumes end beside the others.
-int merge_groups(const MergeArgs &args)
+// average does, whose few large subvolumes end beside the others.  (The runs, and
+// with them the sums, do not depend on it.)
+int merge_waves(const MergeArgs &args)
 {
-    const uint64_t items = args.nsub <= 2048
-                               ? args.most
-                               : static_cast<uint64_t>(args.nitems) / args.nsub;
-    const uint64_t batches = (items + kMergeBatch - 1) / kMergeBatch;
-    return batches <= 1 ? 1 : batches <= 4 ? 4 : 16;
+    if (!args.most)
+        return 1;
+    return static_cast<int>(merge_runs(args.nsub <= 2048
+                                           ? args.most
+                                           : static_cast<uint64_t>(args.nitems) / args.nsub));
+}
+
+// LDS that the runs' sums of the list's largest subvolume take.
+uint32_t merge_lds(const MergeArgs &args, int waves)
+{
+    return waves == 1 ? 0 : merge_runs(args.most) * merge_fields(args) * 2 * sizeof(double);
 }
 
 }  // namespace
@@ -484,40 +512,44 @@ hipError_t launch_merge(const MergeArgs &args, hipStream_t stream)
 {
     if (args.nsub == 0)
         return hipSuccess;
-    if (!merge_fits(args))
+    if (merge_fields(args) > kMergeMaxFields)
         return hipErrorInvalidValue;
-    const int groups = merge_groups(args);
-    if (groups == 1)
-        hipLaunchKernelGGL(merge_kernel<1>, dim3(args.nsub), dim3(64), 0, stream, args);
-    else if (groups == 4)
-        hipLaunchKernelGGL(merge_kernel<4>, dim3(args.nsub), dim3(256), 0, stream, args);
+    const int waves = merge_waves(args);
+    const uint32_t lds = merge_lds(args, waves);
+    const dim3 grid(args.nsub), block(64 * waves);
+    if (waves == 1)
+        hipLaunchKernelGGL(merge_kernel<1>, grid, block, lds, stream, args);
+    else if (waves == 4)
+        hipLaunchKernelGGL(merge_kernel<4>, grid, block, lds, stream, args);
     else
-        hipLaunchKernelGGL(merge_kernel<16>, dim3(args.nsub), dim3(1024), 0, stream, args);
+        hipLaunchKernelGGL(merge_kernel<16>, grid, block, lds, stream, args);
     return hipGetLastError();
 }
 
 hipError_t launch_merges(const MergeArgs *args, size_t n, hipStream_t stream)
 {
-    for (const int groups : {1, 4, 16}) {
+    for (const int waves : {1, 4, 16}) {
         MergeLists l{};
+        uint32_t lds = 0;
         auto flush = [&]() -> hipError_t {
             if (l.n == 0)
                 return hipSuccess;
-            const dim3 grid(l.first[l.n]);
-            if (groups == 1)
-                hipLaunchKernelGGL(merge_lists_kernel<1>, grid, dim3(64), 0, stream, l);
-            else if (groups == 4)
-                hipLaunchKernelGGL(merge_lists_kernel<4>, grid, dim3(256), 0, stream, l);
+            const dim3 grid(l.first[l.n]), block(64 * waves);
+            if (waves == 1)
+                hipLaunchKernelGGL(merge_lists_kernel<1>, grid, block, lds, stream, l);
+            else if (waves == 4)
+                hipLaunchKernelGGL(merge_lists_kernel<4>, grid, block, lds, stream, l);
             else
-                hipLaunchKernelGGL(merge_lists_kernel<16>, grid, dim3(1024), 0, stream, l);
+                hipLaunchKernelGGL(merge_lists_kernel<16>, grid, block, lds, stream, l);
             l.n = 0;
+            lds = 0;
             return hipGetLastError();
         };
         for (size_t i = 0; i < n; ++i) {
             const MergeArgs &m = args[i];
-            if (m.nsub == 0 || merge_groups(m) != groups)
+            if (m.nsub == 0 || merge_waves(m) != waves)
                 continue;
-            if (!merge_fits(m))
+            if (merge_fields(m) > kMergeMaxFields)
                 return hipErrorInvalidValue;
             // (a grid of at most 2^31 - 1 blocks)
             if (l.n == kMergeLists || (l.n && l.first[l.n] > 0x7FFFFFFFu - m.nsub)) {
@@ -528,6 +560,7 @@ hipError_t launch_merges(const MergeArgs *args, size_t n, hipStream_t stream)
             l.list[l.n] = m;
             l.first[l.n + 1] = l.first[l.n] + m.nsub;
             ++l.n;
+            lds = std::max(lds, merge_lds(m, waves));
         }
         const hipError_t e = flush();
         if (e != hipSuccess)

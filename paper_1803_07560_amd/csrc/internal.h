@@ -86,7 +86,8 @@ struct MergeArgs {
     double *sub_rec;            // nsub x rec_len
     double *sub_split;          // nsub x (1 + 2d) or null
     uint32_t nsub;
-    uint32_t nitems, most;      // items of the whole list, and of its largest subvolume
+    uint32_t nitems, most;      // items of the whole list, and of its largest subvolume;
+                                // both 0: one run per subvolume (see merge_kernel)
     int32_t nx, d;
 };
 

@@ -326,8 +326,9 @@ bfi_status ResidentEval::enqueue(size_t nsub, uint64_t nitems, hipStream_t st)
     m.sub_rec = d_sub_rec_;
     m.sub_split = split_ ? d_sub_split_ : nullptr;
     m.nsub = static_cast<uint32_t>(nsub);
-    // nitems and most stay 0, so every list takes the one-wavefront merge: another
-    // kernel from round to round could not be updated in place
+    // nitems and most stay 0, so every subvolume is one run (sums that decide keep one
+    // order) and every list takes the same kernel: another one from round to round
+    // could not be updated in place
     m.nx = lat_.nx;
     m.d = d_;
     BFI_HIP(launch_merge(m, st));

@@ -353,7 +353,7 @@ struct bfi_plan {
     uint32_t nitems = 0, most_items = 0;  // of the list, and of its largest subvolume
     bool direct = false;  // d_sub_rec, d_sub_split in the call's pinned block
     bool queue = false;  // items through the queue (item_queue)
-    bool fixed_order = false;  // one-wavefront merge: sums in the launch shape's order
+    bool fixed_order = false;  // merged in one run: sums in the launch shape's order
     uint32_t grid = 0;
     uint64_t n_evals = 0;
 
@@ -437,7 +437,7 @@ bfi_status plan_build(bfi_context *ctx, const bfi_lattice &lat, int prec,
 // One blocking evaluation of a list on the context's stream: records to
 // `partials`, split statistics to `split` when non-NULL.
 //   eval_once: the lattice action over boxes.  fixed_order: items of the launch
-//     shape and a merge by one wavefront, for callers that decide by the split
+//     shape and a merge in one run, for callers that decide by the split
 //     statistics.  Where a few samples carry a subvolume's weight, two
 //     dimensions' spreads are equal but for the last bits of the sums, and
 //     another order of summation would suggest another dimension.

@@ -43,6 +43,7 @@
 #include <numeric>
 #include <optional>
 
+#include "launch_limits.h"
 #include "runtime.h"
 
 using namespace bfi;
@@ -488,8 +489,9 @@ public:
     // room for n leaves; the first `keep` leaves' records are kept
     bfi_status reserve(size_t n, size_t keep)
     {
-        if (n > 0xFFFFFFFFull)
-            return fail(BFI_EINVAL, "more than 2^32 leaves");
+        if (n > kMaxLeaves)
+            return fail(BFI_EINVAL, "more than %llu leaves",
+                        static_cast<unsigned long long>(kMaxLeaves));
         if (n <= cap_ && rec_)
             return BFI_OK;
         // capacities in elements; every per-leaf buffer grows to the same count
@@ -539,7 +541,7 @@ public:
     // device time of the last fold and this analysis
     bfi_status analyse(size_t count, bfi_result *res, double *device_ms)
     {
-        if (count == 0 || count > 0xFFFFFFFFull)
+        if (count == 0 || count > kMaxLeaves)
             return fail(BFI_EINVAL, "leaf count out of range");
         hipStream_t st = ctx_->stream;
         BFI_TRY(events());

@@ -6,6 +6,7 @@
 
 #include "bfi.h"
 #include "device.hpp"
+#include "launch_limits.h"
 
 namespace bfi {
 namespace {
@@ -489,15 +490,16 @@ int merge_fields(const MergeArgs &args)
 // Wavefronts per subvolume: one for one batch of items, four for up to four,
 // else sixteen.  The largest subvolume decides while the blocks fit the chip
 // together (2048 of up to 16 wavefronts are four rounds); of longer lists the
-// average does, whose few large subvolumes end beside the others.  (The runs, and
-// with them the sums, do not depend on it.)
+// average does, whose few large subvolumes end beside the others; and lists too long
+// for a launch of so many take fewer.  (The runs, and with them the sums, do not
+// depend on it.)
 int merge_waves(const MergeArgs &args)
 {
     if (!args.most)
         return 1;
-    return static_cast<int>(merge_runs(args.nsub <= 2048
-                                           ? args.most
-                                           : static_cast<uint64_t>(args.nitems) / args.nsub));
+    const uint64_t items =
+        args.nsub <= 2048 ? args.most : static_cast<uint64_t>(args.nitems) / args.nsub;
+    return fitting_waves(args.nsub, static_cast<int>(merge_runs(items)));
 }
 
 // LDS that the runs' sums of the list's largest subvolume take.
@@ -551,8 +553,8 @@ hipError_t launch_merges(const MergeArgs *args, size_t n, hipStream_t stream)
                 continue;
             if (merge_fields(m) > kMergeMaxFields)
                 return hipErrorInvalidValue;
-            // (a grid of at most 2^31 - 1 blocks)
-            if (l.n == kMergeLists || (l.n && l.first[l.n] > 0x7FFFFFFFu - m.nsub)) {
+            const uint64_t most_blocks = kMaxThreads / (64 * waves);
+            if (l.n == kMergeLists || (l.n && uint64_t(l.first[l.n]) + m.nsub > most_blocks)) {
                 const hipError_t e = flush();
                 if (e != hipSuccess)
                     return e;

@@ -7,6 +7,7 @@
 // the order of the sums over leaves differs (tree sums per wavefront, groups of
 // wavefronts in order with Neumaier compensation).
 #include "device.hpp"
+#include "launch_limits.h"
 
 #pragma clang fp contract(off)
 
@@ -47,7 +48,7 @@ constexpr int kFoldBlock = 256;
 
 __global__ void __launch_bounds__(kFoldBlock) fold_kernel(FoldArgs a)
 {
-    const uint32_t i = (blockIdx.x * kFoldBlock + threadIdx.x) >> 6;
+    const uint32_t i = blockIdx.x * (kFoldBlock / 64) + (threadIdx.x >> 6);
     const int lane = static_cast<int>(threadIdx.x & 63u);
     if (i >= a.count)
         return;
@@ -318,13 +319,15 @@ __device__ void split_choice(const LeafAnalysisArgs &a, uint32_t s, int j)
 }
 
 // The first `sum_blocks` blocks sum the second pass, a thread per leaf; the
-// others make the split choices, half a wavefront per leaf.
+// others make the split choices from leaf `first` on, half a wavefront per leaf.
 __global__ void __launch_bounds__(kPassBlock) second_pass_kernel(LeafAnalysisArgs a,
-                                                                 uint32_t sum_blocks)
+                                                                 uint32_t sum_blocks,
+                                                                 uint32_t first)
 {
     const int lane = static_cast<int>(threadIdx.x & 63u);
     if (blockIdx.x >= sum_blocks) {
-        const uint32_t s = ((blockIdx.x - sum_blocks) * kPassBlock + threadIdx.x) >> 5;
+        const uint32_t s =
+            first + (blockIdx.x - sum_blocks) * (kPassBlock / 32) + (threadIdx.x >> 5);
         if (s < a.count)
             split_choice(a, s, lane & 31);
         return;
@@ -387,9 +390,15 @@ hipError_t launch_fold(const FoldArgs &args, hipStream_t stream)
         return hipSuccess;
     if (args.nx < 1 || args.nx > kMaxAnalysisNx || args.d < 1 || args.d > 32)
         return hipErrorInvalidValue;
-    const size_t grid = (static_cast<size_t>(args.count) * 64 + kFoldBlock - 1) / kFoldBlock;
-    hipLaunchKernelGGL(fold_kernel, dim3(static_cast<uint32_t>(grid)), dim3(kFoldBlock), 0, stream, args);
-    return hipGetLastError();
+    return for_slices(args.count, kFoldSlice, hipSuccess, [&](uint32_t first, uint32_t n) {
+        FoldArgs part = args;
+        part.entries += first;
+        part.count = n;
+        const uint32_t per_block = kFoldBlock / 64;
+        hipLaunchKernelGGL(fold_kernel, dim3((n + per_block - 1) / per_block), dim3(kFoldBlock), 0,
+                           stream, part);
+        return hipGetLastError();
+    });
 }
 
 size_t analysis_scratch_doubles(uint32_t count, int nx)
@@ -401,7 +410,8 @@ size_t analysis_scratch_doubles(uint32_t count, int nx)
 
 hipError_t launch_leaf_analysis(const LeafAnalysisArgs &args, hipStream_t stream)
 {
-    if (args.count == 0 || args.nx < 1 || args.nx > kMaxAnalysisNx || args.d < 1 || args.d > 32)
+    if (args.count == 0 || args.count > kMaxLeaves || args.nx < 1 || args.nx > kMaxAnalysisNx ||
+        args.d < 1 || args.d > 32)
         return hipErrorInvalidValue;
     auto blocks = [&](size_t threads, size_t block) {
         return static_cast<uint32_t>((threads + block - 1) / block);
@@ -415,11 +425,23 @@ hipError_t launch_leaf_analysis(const LeafAnalysisArgs &args, hipStream_t stream
         hipLaunchKernelGGL(shift_reduce_kernel<false>, dim3(1), dim3(kAnalysisBlock), 0, stream,
                            args);
     }
-    const uint32_t sums = blocks(count, kPassBlock), choices = blocks(32 * count, kPassBlock);
+    const uint32_t sums = blocks(count, kPassBlock);
     hipLaunchKernelGGL(first_pass_kernel, dim3(sums), dim3(kPassBlock), 0, stream, args);
     hipLaunchKernelGGL(first_reduce_kernel, dim3(1), dim3(kAnalysisBlock), 0, stream, args);
-    hipLaunchKernelGGL(second_pass_kernel, dim3(sums + choices), dim3(kPassBlock), 0, stream, args,
-                       sums);
+    // sums and choices in one launch, or apart where that is too long for one
+    const uint32_t beside = args.count <= kChoiceSlice ? sums : 0;
+    if (!beside)
+        hipLaunchKernelGGL(second_pass_kernel, dim3(sums), dim3(kPassBlock), 0, stream, args, sums,
+                           0u);
+    const hipError_t e =
+        for_slices(args.count, kChoiceSlice, hipSuccess, [&](uint32_t first, uint32_t n) {
+            hipLaunchKernelGGL(second_pass_kernel,
+                               dim3(beside + blocks(32 * static_cast<size_t>(n), kPassBlock)),
+                               dim3(kPassBlock), 0, stream, args, beside, first);
+            return hipGetLastError();
+        });
+    if (e != hipSuccess)
+        return e;
     hipLaunchKernelGGL(second_reduce_kernel, dim3(1), dim3(kAnalysisBlock), 0, stream, args);
     return hipGetLastError();
 }

@@ -315,9 +315,10 @@ uint64_t item_samples(const bfi_launch &l, bool spread, bool split, const uint64
             continue;
         last = m;
         const uint64_t chunk = m * block;
+        const ItemCount count(chunk);
         uint64_t items = 0;
         for (size_t s = 0; s < nsub; ++s)
-            items += n[s] / chunk + (n[s] % chunk != 0);
+            items += count(n[s]);
         // two estimates of the time of blocks that take the next item as they go,
         // the longest first: whole rounds of the longest item (and a sixteenth of
         // one: the blocks do not run equally fast, so that few long rounds end
@@ -338,24 +339,39 @@ uint64_t item_samples(const bfi_launch &l, bool spread, bool split, const uint64
 void list_items(uint64_t chunk, const uint64_t *n, size_t nsub, const EvalParams *params,
                 double *item_rec, int rec_len, uint32_t *first, WorkItem *items)
 {
+    // rests by 64ths of a whole item: their places from a count, so that the order
+    // costs a pass over the list whatever its length
+    constexpr uint64_t kClasses = 64;
     uint64_t whole = 0;
-    for (size_t s = 0; s < nsub; ++s)
+    std::array<uint64_t, kClasses> place{};
+    for (size_t s = 0; s < nsub; ++s) {
         whole += n[s] / chunk;
-    WorkItem *w = items, *const rests = items + whole, *r = rests;
+        const uint64_t rest = n[s] % chunk;
+        place[rest * kClasses / chunk] += rest != 0;
+    }
+    uint64_t at = whole;
+    for (size_t c = kClasses; c-- > 0;) {
+        const uint64_t here = place[c];
+        place[c] = at;
+        at += here;
+    }
+    WorkItem *w = items;
     uint32_t slot = 0;
     for (size_t s = 0; s < nsub; ++s) {
         first[s] = slot;
-        for (uint64_t start = 0; start < n[s]; start += chunk, ++slot) {
-            const uint64_t count = std::min(chunk, n[s] - start);
-            *(count == chunk ? w : r)++ =
-                WorkItem{params, item_rec + static_cast<size_t>(slot) * rec_len, start,
-                         static_cast<uint32_t>(s), static_cast<uint32_t>(count)};
-        }
+        uint64_t start = 0;
+        auto item = [&](uint64_t count) {
+            const WorkItem it{params, item_rec + static_cast<size_t>(slot++) * rec_len, start,
+                              static_cast<uint32_t>(s), static_cast<uint32_t>(count)};
+            start += count;
+            return it;
+        };
+        while (n[s] - start >= chunk)
+            *w++ = item(chunk);
+        if (const uint64_t rest = n[s] - start)
+            items[place[rest * kClasses / chunk]++] = item(rest);
     }
     first[nsub] = slot;
-    const auto longer = [](const WorkItem &a, const WorkItem &b) { return a.count > b.count; };
-    if (!std::is_sorted(rests, r, longer))
-        std::stable_sort(rests, r, longer);
 }
 
 namespace {

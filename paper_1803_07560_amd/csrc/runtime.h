@@ -149,6 +149,22 @@ inline bool spread_items(int prec, const bfi_launch *req)
 {
     return prec == kFP64 && !(req && req->samples_per_thread > 0);
 }
+// Work items of n samples in chunks, without an integer division: exact below 2^48
+// samples of chunks below 2^31 (the quotient, raised by 2^-49, lies above the true
+// one and by less than 1/chunk).  A list's size is asked for up to six times:
+// 10^4 subvolumes 0.15 -> 0.05 ms.
+struct ItemCount {
+    double inverse;
+    explicit ItemCount(uint64_t chunk) : inverse((1.0 + 0x1p-49) / static_cast<double>(chunk)) {}
+    uint64_t operator()(uint64_t n) const
+    {
+        if (n == 0)
+            return 0;
+        return static_cast<uint64_t>(
+                   static_cast<int64_t>(static_cast<double>(static_cast<int64_t>(n - 1)) * inverse)) +
+               1;
+    }
+};
 // Samples per work item of a list of sample counts, at most the launch shape's
 // samples_per_thread x block.  The tuned shapes are those of long runs, whose
 // items hold 2^16 samples and more; a list of fewer than eight rounds of such
@@ -190,10 +206,12 @@ inline bool item_queue(const bfi_launch &l, const bfi_launch *req, uint64_t chun
 // Work items of a list: record slots in list order (sub_first: first slot of each
 // subvolume, nsub + 1 entries), the items themselves in the order in which blocks
 // shall take them, whole ones first and then the subvolumes' rests by falling
-// length, so that the last round ends on the shortest.  (The records do not
-// depend on the order.)  Measured, list order -> this, whole calls: 2^26
+// length (in 64ths of a whole one), so that the last round ends on the shortest.
+// (The records do not depend on the order.)  Measured, list order -> this, whole calls: 2^26
 // evaluations of the Gaussian-proposal sampler over 512 streams 1.38 -> 1.33 ms,
-// 301 uneven leaves with split statistics 257 -> 250 us.
+// 301 uneven leaves with split statistics 257 -> 250 us.  The order is a count's,
+// not a sort's, since long lists gain nothing by it: 10^4 ragged leaves are listed
+// in 0.07 ms (a stable sort of the rests 0.79), 10^6 in 10 (124).
 void list_items(uint64_t chunk, const uint64_t *n, size_t nsub, const EvalParams *params,
                 double *item_rec, int rec_len, uint32_t *sub_first, WorkItem *items);
 

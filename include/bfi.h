@@ -206,8 +206,8 @@ bfi_status bfi_eval(bfi_context *ctx, const bfi_lattice *lat, bfi_precision prec
 
 /* bfi_eval for callers that cannot allocate: code under stream capture, tight
  * serving loops, harnesses that forbid hipMalloc.  Same arguments, validation,
- * launch resolution, kernels and results as bfi_eval (with the same launch
- * shape the records are bitwise equal); blocking on the context's stream.  It
+ * launch resolution, work items, kernels and results as bfi_eval (the records
+ * are bitwise equal); blocking on the context's stream.  It
  * calls no hipMalloc, hipFree or other allocating routine: the copied
  * subvolume list, point maps, work items, item and subvolume records and the
  * queue head live in one static device array of BFI_NOALLOC_SCRATCH_BYTES per
@@ -218,9 +218,8 @@ bfi_status bfi_eval(bfi_context *ctx, const bfi_lattice *lat, bfi_precision prec
  * parameter block, (count + 1) first-item indices, work items (32 B), item
  * records (BFI_PARTIAL_LEN(nx) doubles each, plus 2d with split statistics),
  * subvolume records (plus BFI_SPLIT_LEN(d) with split statistics), the queue
- * head.  Items are bfi_eval's; where they are smaller than the launch shape's
- * (see bfi_launch) and their layout exceeds the array, the launch shape's
- * items are taken.
+ * head.  (Lists whose smaller items, see bfi_launch, exceed the array where the
+ * launch shape's do not take the launch shape's, here and in bfi_eval.)
  * Every call on a device shares that device's array: calls that overlap in
  * time on one device (from two threads or two contexts) race.  Errors: those
  * of bfi_eval, and EINVAL (with the bytes needed) when the layout exceeds the

@@ -10,9 +10,9 @@
 // (noalloc_setup) and only that address is passed to kernels and copies: in
 // host code the array's name is a host-side stand-in, not device memory.
 // Point maps and work items are built on the device from the copied list
-// (launch_build_items), so the host needs no staging either.  The kernels that evaluate, reduce and
-// merge are bfi_eval's own, so with the same launch shape the records are the
-// same bits.
+// (launch_build_items), so the host needs no staging either.  The kernels that
+// evaluate, reduce and merge are bfi_eval's own, and so are the items
+// (cut_lattice_items), so the records are the same bits.
 //
 // Every call on a device shares that device's array and leaves its contents
 // there; calls that overlap in time on one device (two threads, two contexts
@@ -74,6 +74,11 @@ Layout layout_for(size_t nsub, int d, int rec_len, uint64_t nitems, bool split)
 }
 
 }  // namespace
+
+size_t noalloc_bytes(size_t nsub, int d, int rec_len, uint64_t nitems, bool split)
+{
+    return layout_for(nsub, d, rec_len, nitems, split).total;
+}
 
 bfi_status noalloc_setup(int device)
 {
@@ -142,30 +147,22 @@ extern "C" bfi_status bfi_eval_noalloc(bfi_context *ctx, const bfi_lattice *lat,
                                   std::max(ctx->cu_count, 1);
         const size_t nsub = subs->count;
         const int rec_len = BFI_PARTIAL_LEN(lat->nx);
-        bool spread = spread_items(prec, launch);
-        uint64_t chunk = 0, nitems = 0, most = 0;
-        Layout L{};
-        for (;;) {
-            chunk = item_samples(l, spread, split != nullptr, subs->n, nsub, resident);
-            nitems = most = 0;
-            for (size_t s = 0; s < nsub; ++s) {
-                const uint64_t count = subs->n[s] / chunk + (subs->n[s] % chunk != 0);
-                nitems += count;
-                most = std::max(most, count);
-                if (nitems > 0x7FFFFFFFull)
-                    return fail(BFI_EINVAL, "more than 2^31 work items; raise samples_per_thread");
-            }
-            L = layout_for(nsub, d, rec_len, nitems, split != nullptr);
-            // a list whose shorter items do not fit keeps the launch shape's items
-            if (L.total <= kScratchBytes || !spread)
-                break;
-            spread = false;
-        }
-        if (L.total > kScratchBytes)
+        const bool spread = spread_items(prec, launch);
+        ItemCut cut =
+            cut_lattice_items(l, spread, split != nullptr, d, rec_len, subs->n, nsub, resident);
+        if (cut.nitems > 0x7FFFFFFFull)
+            return fail(BFI_EINVAL, "more than 2^31 work items; raise samples_per_thread");
+        Layout L = layout_for(nsub, d, rec_len, cut.nitems, split != nullptr);
+        if (L.total > kScratchBytes) {
+            // (the least it needs: the launch shape's items)
+            cut = cut_items(l, false, split != nullptr, subs->n, nsub, resident);
+            L = layout_for(nsub, d, rec_len, cut.nitems, split != nullptr);
             return fail(BFI_EINVAL,
                         "the evaluation needs %zu bytes of scratch (%zu subvolumes, %llu work "
                         "items); the allocation-free entry point holds at most %zu",
-                        L.total, nsub, static_cast<unsigned long long>(nitems), kScratchBytes);
+                        L.total, nsub, static_cast<unsigned long long>(cut.nitems), kScratchBytes);
+        }
+        const uint64_t chunk = cut.chunk, nitems = cut.nitems;
 
         hipStream_t st = ctx->stream;
         auto at = [&](size_t off) { return static_cast<void *>(base + off); };
@@ -225,7 +222,7 @@ extern "C" bfi_status bfi_eval_noalloc(bfi_context *ctx, const bfi_lattice *lat,
         m.sub_split = sub_split;
         m.nsub = static_cast<uint32_t>(nsub);
         m.nitems = static_cast<uint32_t>(nitems);
-        m.most = static_cast<uint32_t>(most);
+        m.most = static_cast<uint32_t>(cut.most);
         m.nx = lat->nx;
         m.d = d;
         BFI_HIP(launch_merge(m, st));

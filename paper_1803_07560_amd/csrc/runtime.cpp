@@ -336,6 +336,33 @@ uint64_t item_samples(const bfi_launch &l, bool spread, bool split, const uint64
     return best;
 }
 
+ItemCut cut_items(const bfi_launch &l, bool spread, bool split, const uint64_t *n, size_t nsub,
+                  uint64_t resident)
+{
+    ItemCut cut{item_samples(l, spread, split, n, nsub, resident), 0, 0};
+    for (size_t s = 0; s < nsub; ++s) {
+        const uint64_t count = n[s] / cut.chunk + (n[s] % cut.chunk != 0);
+        cut.nitems += count;
+        cut.most = std::max(cut.most, count);
+        if (cut.nitems > 0x7FFFFFFFull)  // (refused by the caller; the count cannot wrap)
+            break;
+    }
+    return cut;
+}
+
+ItemCut cut_lattice_items(const bfi_launch &l, bool spread, bool split, int d, int rec_len,
+                          const uint64_t *n, size_t nsub, uint64_t resident)
+{
+    const auto fits = [&](const ItemCut &c) {
+        return noalloc_bytes(nsub, d, rec_len, c.nitems, split) <= BFI_NOALLOC_SCRATCH_BYTES;
+    };
+    const ItemCut cut = cut_items(l, spread, split, n, nsub, resident);
+    if (!spread || fits(cut))
+        return cut;
+    const ItemCut whole = cut_items(l, false, split, n, nsub, resident);
+    return fits(whole) ? whole : cut;
+}
+
 void list_items(uint64_t chunk, const uint64_t *n, size_t nsub, const EvalParams *params,
                 double *item_rec, int rec_len, uint32_t *first, WorkItem *items)
 {
@@ -724,19 +751,16 @@ bfi_status plan_build_core(bfi_context *ctx, const PlanSpec &what, const bfi_sub
                                        lat.antithetic},
                             &resident));
 
-    // work items: ceil(n / chunk) per subvolume, subvolumes in list order
-    const uint64_t chunk = item_samples(l, spread_items(prec, launch) && !what.fixed_order, split,
-                                        subs.n, nsub, resident);
-    uint64_t nitems = 0, most = 0, n_evals = 0;
-    for (size_t s = 0; s < nsub; ++s) {
-        // checked per subvolume, so the running count cannot wrap
-        const uint64_t count = subs.n[s] / chunk + (subs.n[s] % chunk != 0);
-        nitems += count;
-        if (nitems > 0x7FFFFFFFull)
-            return fail(BFI_EINVAL, "more than 2^31 work items; raise samples_per_thread");
-        most = std::max(most, count);
+    const bool spread = spread_items(prec, launch) && !what.fixed_order;
+    const ItemCut cut = kind == 0 ? cut_lattice_items(l, spread, split, d, BFI_PARTIAL_LEN(what.nx),
+                                                      subs.n, nsub, resident)
+                                  : cut_items(l, spread, split, subs.n, nsub, resident);
+    const uint64_t chunk = cut.chunk, nitems = cut.nitems;
+    if (nitems > 0x7FFFFFFFull)
+        return fail(BFI_EINVAL, "more than 2^31 work items; raise samples_per_thread");
+    uint64_t n_evals = 0;
+    for (size_t s = 0; s < nsub; ++s)
         n_evals += subs.n[s];
-    }
     if (lat.antithetic)
         n_evals *= 2;  // two points per sample index
 
@@ -798,7 +822,7 @@ bfi_status plan_build_core(bfi_context *ctx, const PlanSpec &what, const bfi_sub
     p->nsub = nsub;
     p->launch = l;
     p->nitems = static_cast<uint32_t>(nitems);
-    p->most_items = static_cast<uint32_t>(most);
+    p->most_items = static_cast<uint32_t>(cut.most);
     p->fixed_order = what.fixed_order;
     p->n_evals = n_evals;
     p->d_params = reinterpret_cast<EvalParams *>(dev + o_params);

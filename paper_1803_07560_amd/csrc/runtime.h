@@ -183,6 +183,22 @@ struct ItemCount {
 uint64_t item_samples(const bfi_launch &l, bool spread, bool split, const uint64_t *n, size_t nsub,
                       uint64_t resident);
 
+// A list's items: their size, how many there are, how many its largest subvolume
+// has.
+struct ItemCut {
+    uint64_t chunk, nitems, most;
+};
+ItemCut cut_items(const bfi_launch &l, bool spread, bool split, const uint64_t *n, size_t nsub,
+                  uint64_t resident);
+// The items of a list of lattice subvolumes, for every entry point alike: shorter
+// ones (spread) unless only the launch shape's fit the allocation-free entry
+// point's array, so that its records are those of the others on every list that
+// it takes.
+ItemCut cut_lattice_items(const bfi_launch &l, bool spread, bool split, int d, int rec_len,
+                          const uint64_t *n, size_t nsub, uint64_t resident);
+// Bytes of that array for a list (noalloc.hip).
+size_t noalloc_bytes(size_t nsub, int d, int rec_len, uint64_t nitems, bool split);
+
 // Rounds of items over the resident blocks from which a list counts as long: the
 // last round and the start no longer matter.
 constexpr uint64_t kRounds = 8;

@@ -108,15 +108,11 @@ bfi_status sph_eval(bfi_context *ctx, const bfi_lattice &lat, int prec, uint64_t
     LaunchSpec spec{prec, l.block, 0, l.persistent, 0, lat.observable, 0};
     uint64_t resident = 0;
     BFI_TRY(resident_blocks(ctx, 3, lat, spec, &resident));
-    const uint64_t chunk = item_samples(l, spread_items(prec, launch), false, sh.n, ns, resident);
-    uint64_t nitems = 0, most = 0;
-    for (size_t s = 0; s < ns; ++s) {
-        const uint64_t count = sh.n[s] / chunk + (sh.n[s] % chunk != 0);
-        nitems += count;
-        most = std::max(most, count);
-        if (nitems > 0x7FFFFFFFull)
-            return fail(BFI_EINVAL, "more than 2^31 work items; raise samples_per_thread");
-    }
+    const ItemCut cut =
+        cut_items(l, spread_items(prec, launch), false, sh.n, ns, resident);
+    const uint64_t chunk = cut.chunk, nitems = cut.nitems;
+    if (nitems > 0x7FFFFFFFull)
+        return fail(BFI_EINVAL, "more than 2^31 work items; raise samples_per_thread");
 
     // one device block: what the host writes first (parameters, ids, offsets,
     // shells, items, queue head), then the records
@@ -180,7 +176,7 @@ bfi_status sph_eval(bfi_context *ctx, const bfi_lattice &lat, int prec, uint64_t
     m.sub_rec = reinterpret_cast<double *>((direct ? img : base) + o_srec);
     m.nsub = static_cast<uint32_t>(ns);
     m.nitems = static_cast<uint32_t>(nitems);
-    m.most = static_cast<uint32_t>(most);
+    m.most = static_cast<uint32_t>(cut.most);
     m.nx = lat.nx;
     m.d = d;
     BFI_HIP(launch_merge(m, st));

@@ -245,7 +245,10 @@ bfi_status bfi_plan_create(bfi_context *ctx, const bfi_lattice *lat, bfi_precisi
 bfi_status bfi_plan_run(bfi_plan *plan, uint64_t seed, double *partials_dev, void *stream);
 /* Wait for the plan's last run and copy its partial records to host. */
 bfi_status bfi_plan_partials(bfi_plan *plan, double *partials);
-/* Work items of the plan and the launch shape it resolved to. */
+/* Work items of the plan, as cut, and the launch shape that it resolved to (given
+ * or tuned): where that leaves samples_per_thread or persistent open, the items
+ * may be smaller and the queue unused, as bfi_launch says.  Given to another plan
+ * or evaluation in full, the shape is taken as it is. */
 bfi_status bfi_plan_info(const bfi_plan *plan, uint64_t *n_items, uint64_t *n_evals,
                          bfi_launch *resolved);
 /* Duration in milliseconds of the plan's last run on the device, from HIP

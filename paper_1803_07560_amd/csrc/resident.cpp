@@ -14,6 +14,7 @@
 // and a kernel that reset the queue head cost each of a round's two replays some
 // 30 us, and each run the pinning of twice eight buffers: a run of 2^28
 // evaluations over 8 rounds 9.7 -> 8.2 ms without them.)
+#include "launch_limits.h"
 #include "runtime.h"
 
 #include <algorithm>
@@ -129,7 +130,7 @@ bfi_status ResidentEval::init(bfi_context *ctx, const bfi_lattice &lat, int prec
     launch_ = resolve_launch(ctx, lat, prec, split, launch);
     launch_.use_graph = 1;
     launch_.persistent = 1;
-    asked_ = launch && launch->persistent >= 0;
+    asked_ = launch && launch->persistent >= 0 ? launch->persistent != 0 : -1;
     if (!mc_block_ok(launch_.block))
         return fail(BFI_EINVAL, "block must be 64, 128, 256, 512 or 1024 (got %d)", launch_.block);
     if (launch_.samples_per_thread < 1 || launch_.samples_per_thread > (1 << 20))
@@ -305,8 +306,9 @@ bfi_status ResidentEval::enqueue(size_t nsub, uint64_t nitems, hipStream_t st)
                  d_scale64_, d_base32_, d_scale32_, d_items_, params, d_item_rec_, chunk_,
                  static_cast<uint32_t>(nsub), d_, rec_len_};
     BFI_HIP(launch_build_items(ba, st));
-    const bool queue =
-        asked_ || item_queue(launch_, nullptr, chunk_, nitems, resident_blocks_);
+    // (a block per item as asked, as far as a launch reaches)
+    const bool queue = asked_ < 0 ? item_queue(launch_, nullptr, chunk_, nitems, resident_blocks_)
+                                  : asked_ == 1 || nitems * launch_.block > kMaxThreads;
     LaunchSpec spec{prec_, launch_.block, split_ ? 1 : 0, queue ? 1 : 0,
                     static_cast<uint32_t>(
                         queue ? std::min<uint64_t>(resident_blocks_, nitems) : nitems),

@@ -319,7 +319,7 @@ private:
     bfi_lattice lat_{};
     int prec_ = 0, d_ = 0, rec_len_ = 0, split_len_ = 0;
     bool split_ = false, copy_records_ = true;
-    bool asked_ = false;  // the caller chose the queue (else item_queue does)
+    int asked_ = -1;  // 1, 0: the caller chose the queue or a block per item; -1: item_queue
     bfi_launch launch_{};
     uint64_t chunk_ = 0, resident_blocks_ = 0;
     size_t count_ = 0;

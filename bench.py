@@ -138,6 +138,9 @@ def parse():
                     help="skip the antithetic-pair leg")
     ap.add_argument("--calibrate-copy-mib", type=int, default=0,
                     help="also run one device copy of this size (counter calibration)")
+    ap.add_argument("--full", action="store_true",
+                    help="print every number of the result in full: per-step times, every "
+                         "field of the adaptive runs, all digits (about 20 kB)")
     ap.add_argument("--tune-cache", default=os.path.join(ROOT, "paper_1803_07560_amd",
                                                          "tuned_gfx950.json"))
     return ap.parse_args()
@@ -594,6 +597,28 @@ def error_vs_oracle(bfi, ctx, w, sub, rec):
     return out
 
 
+def short_line(line):
+    """The result line at a length that a log keeps whole (about 10 kB): the value and
+    its time as they are, other numbers to six digits, the adaptive runs by
+    their outcome, no per-step lists."""
+    runs = ("form", "observable", "nu", "seed", "target", "status", "rel_err", "seconds")
+
+    def short(x):
+        if isinstance(x, float):
+            return float(f"{x:.6g}")
+        if isinstance(x, dict):
+            return {k: short(v) for k, v in x.items() if k not in ("step_ms_each", "kernel_ms_each")}
+        return [short(v) for v in x] if isinstance(x, (list, tuple)) else x
+
+    out = {k: short(v) for k, v in line.items()}
+    for k in ("value", "ms_per_step"):
+        out[k] = line[k]
+    for k in ("adaptive", "adaptive_to_target"):
+        if k in out:
+            out[k] = [{f: run[f] for f in runs if f in run} for run in out[k]]
+    return out
+
+
 def main():
     args = parse()
     if args.gpus != 1:
@@ -790,7 +815,7 @@ def main():
             bfi.bfi_tune_load(ctx, args.tune_cache)
         line["error_vs_oracle"] = error_vs_oracle(bfi, ctx, w, sub, rec)
         bfi.bfi_context_destroy(ctx)
-    print(json.dumps(line), flush=True)
+    print(json.dumps(line if args.full else short_line(line)), flush=True)
 
 
 if __name__ == "__main__":

@@ -231,8 +231,9 @@ __global__ void __launch_bounds__(64 * WAVES) merge_kernel(MergeArgs m)
 // Several lists in one launch, their arguments in the kernel's own: list r's
 // subvolumes are blocks first[r] .. first[r + 1] - 1.  A burst of 16 served
 // requests (2^16 .. 2^22 evaluations) ended on 15 merges and as many copies one
-// after another, 22 us a pair, most of it between the launches: 1.01 -> 0.92 ms
-// for the burst with one launch that writes the records to host memory.
+// after another, 22 us a pair, most of it between the launches: 1.18 .. 1.22 ->
+// 1.06 .. 1.13 ms for the burst with one launch that writes the records to host
+// memory.
 constexpr uint32_t kMergeLists = 16;
 struct MergeLists {
     MergeArgs list[kMergeLists];
@@ -277,8 +278,8 @@ __device__ __forceinline__ double sqrt_unit(double a)
 // computed once.  What bounds it is instruction issue.  A kernel for any
 // dimension up to 16 kept 34 sums whatever the dimension, read the map from
 // memory for every coordinate and masked the unused ones: a call of 3.2e7
-// samples in 6 dimensions took 338 us with it, 201 us with this (161 with the
-// shorter items, block launch and merge batches of today).
+// samples in 6 dimensions took 338 us with it, 201 us with this (164 with the
+// block launch and merge batches of today; its items are the launch shape's).
 template <int DIM>
 __global__ void __launch_bounds__(256) nsphere_kernel(McArgs a)
 {

@@ -282,7 +282,9 @@ constexpr float kLog2e = 1.44269504088896340736f;
 
 template <int NX, int NT, int PREC, int BLOCK, bool AVG>
 __global__ void __launch_bounds__(BLOCK)
-    // three waves per SIMD in the FP32 form (4 registers over 168 otherwise)
+    // three waves per SIMD in the FP32 form: 10x2 anchored would take 172 registers
+    // and two waves; held at 168 it spills 16 bytes a lane (2^26 evaluations over
+    // 512 streams 1.63 -> 1.34 ms), the averaged kernel fits by itself
     __attribute__((amdgpu_waves_per_eu(PREC == kFP64 ? 1 : 3))) is_kernel(IsArgs ia)
 {
     using T = std::conditional_t<PREC == kFP64, double, float>;

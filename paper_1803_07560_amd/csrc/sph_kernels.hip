@@ -88,11 +88,13 @@ __device__ __forceinline__ void shell_point(const dev::PhiloxStream &words, uint
         u[k] *= f;
 }
 
-// FP64 takes about 9 registers a site and a third wave of a SIMD ends at 168:
-// up to 16 sites fit by themselves, 20 sites need 181 and are held at 168 for
-// 28 bytes of scratch (10x2, 2^24 samples, 590 -> 582 us over one shell and
-// 2035 -> 1960 over 26; 8x2 with the same bound 877 -> 888,
-// another schedule of the same registers); 24 sites would spill 136 bytes.
+// FP64 takes about 9 registers a site and a third wave of a SIMD ends at 168: up to
+// 16 sites fit by themselves, 24 would spill 136 bytes; between them, of the
+// compiled lattices, lies 10x2, which needs 181 and is held at 168 for 28 bytes of
+// scratch.  2^24 samples over 1, 26 and 64 shells: 506, 531 and 551 us; with two
+// waves 498, 542 and 550; pilot and main pass over 64 shells 617 and 625.  (8x2
+// with the same bound only gets another schedule: 888 us, 877 without, at the
+// time.)
 template <int SITES, int PREC>
 constexpr int kSphWaves = PREC == kFP64 && SITES > 16 && SITES <= 20 ? 3 : 1;
 

@@ -341,7 +341,7 @@ ItemCut cut_items(const bfi_launch &l, bool spread, bool split, const uint64_t *
 {
     ItemCut cut{item_samples(l, spread, split, n, nsub, resident), 0, 0};
     for (size_t s = 0; s < nsub; ++s) {
-        const uint64_t count = n[s] / cut.chunk + (n[s] % cut.chunk != 0);
+        const uint64_t count = n[s] <= cut.chunk ? n[s] != 0 : (n[s] - 1) / cut.chunk + 1;
         cut.nitems += count;
         cut.most = std::max(cut.most, count);
         if (cut.nitems > 0x7FFFFFFFull)  // (refused by the caller; the count cannot wrap)
@@ -357,7 +357,8 @@ ItemCut cut_lattice_items(const bfi_launch &l, bool spread, bool split, int d, i
         return noalloc_bytes(nsub, d, rec_len, c.nitems, split) <= BFI_NOALLOC_SCRATCH_BYTES;
     };
     const ItemCut cut = cut_items(l, spread, split, n, nsub, resident);
-    if (!spread || fits(cut))
+    const uint64_t most = static_cast<uint64_t>(l.samples_per_thread) * l.block;
+    if (cut.chunk == most || fits(cut))
         return cut;
     const ItemCut whole = cut_items(l, false, split, n, nsub, resident);
     return fits(whole) ? whole : cut;
@@ -368,13 +369,17 @@ void list_items(uint64_t chunk, const uint64_t *n, size_t nsub, const EvalParams
 {
     // rests by 64ths of a whole item: their places from a count, so that the order
     // costs a pass over the list whatever its length
-    constexpr uint64_t kClasses = 64;
+    constexpr size_t kClasses = 64;
+    const double per = kClasses / static_cast<double>(chunk);
+    const auto length = [per](uint64_t rest) {  // (rest < chunk, so below kClasses)
+        return static_cast<size_t>(static_cast<int64_t>(static_cast<double>(rest) * per));
+    };
     uint64_t whole = 0;
     std::array<uint64_t, kClasses> place{};
     for (size_t s = 0; s < nsub; ++s) {
-        whole += n[s] / chunk;
-        const uint64_t rest = n[s] % chunk;
-        place[rest * kClasses / chunk] += rest != 0;
+        const uint64_t here = n[s] < chunk ? 0 : n[s] / chunk, rest = n[s] - here * chunk;
+        whole += here;
+        place[length(rest)] += rest != 0;
     }
     uint64_t at = whole;
     for (size_t c = kClasses; c-- > 0;) {
@@ -396,7 +401,7 @@ void list_items(uint64_t chunk, const uint64_t *n, size_t nsub, const EvalParams
         while (n[s] - start >= chunk)
             *w++ = item(chunk);
         if (const uint64_t rest = n[s] - start)
-            items[place[rest * kClasses / chunk]++] = item(rest);
+            items[place[length(rest)]++] = item(rest);
     }
     first[nsub] = slot;
 }

@@ -227,7 +227,7 @@ inline bool item_queue(const bfi_launch &l, const bfi_launch *req, uint64_t chun
 // evaluations of the Gaussian-proposal sampler over 512 streams 1.38 -> 1.33 ms,
 // 301 uneven leaves with split statistics 257 -> 250 us.  The order is a count's,
 // not a sort's, since long lists gain nothing by it: 10^4 ragged leaves are listed
-// in 0.07 ms (a stable sort of the rests 0.79), 10^6 in 10 (124).
+// in 0.07 ms (a stable sort of the rests 0.7), 10^6 in 7 (120).
 void list_items(uint64_t chunk, const uint64_t *n, size_t nsub, const EvalParams *params,
                 double *item_rec, int rec_len, uint32_t *sub_first, WorkItem *items);
 
